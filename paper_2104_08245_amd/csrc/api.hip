@@ -160,6 +160,7 @@ static LaunchArgs make_args(const nolsm_plan *pl, const BatchArgs &b) {
     na.persistent = o.sched == NOLSM_SCHED_PERSISTENT;
     na.pgrid = pl->pgrid;
     na.sym = o.sym_sign ? 1 : 0;
+    na.nt_out = 0;
     na.force_stall = o.debug_force_stall;
     InvArgs &ia = A.ia;
     ia.prec = o.prec;
@@ -172,7 +173,7 @@ static LaunchArgs make_args(const nolsm_plan *pl, const BatchArgs &b) {
     fa.prec = o.prec;
     fa.nfinal = (o.prec == NOLSM_FP16 || o.prec == NOLSM_BF16) ? o.n_final_fp32 : 0;
     fa.rows = o.finish_rows ? 1 : 0;
-    fa.pad_ = 0;
+    fa.mirror = 0;
     ExtractArgs &ea = A.ea;
     ea.Krp = ga.Krp; ea.Kci = ga.Kci; ea.Srp = ga.Srp; ea.Sci = ga.Sci;
     ea.sub_blk = (const int32_t *)(base + pl->o_sub_blk);
@@ -237,8 +238,13 @@ static int enqueue_solve(const nolsm_plan *pl, const BatchArgs &b, const LaunchA
         e = launch_ns_iter(cd, ws, A.na, it, st);
         if (e != hipSuccess) return hip_fail(e, "Newton-Schulz launch");
     }
+    // the symmetric iterates come by their upper tiles: the fused finishing
+    // completes them itself where each workgroup has a submatrix of its own
+    FinishArgs fa = A.fa;
+    fa.mirror = A.na.sym && fa.prec == NOLSM_FP16 && !fa.rows && cd.max_own == 1;
+    if (A.na.sym && !fa.mirror && (e = launch_ns_mirror(cd, ws, st)) != hipSuccess) return hip_fail(e, "mirror launch");
     if (prof) prof->mark(PH_FINISH);
-    if ((e = launch_finish(cd, ws, A.fa, st)) != hipSuccess) return hip_fail(e, "finish launch");
+    if ((e = launch_finish(cd, ws, fa, st)) != hipSuccess) return hip_fail(e, "finish launch");
     if (prof) prof->mark(PH_EXTRACT);
     if ((e = launch_extract(cd, ws, A.ea, st)) != hipSuccess) return hip_fail(e, "extract launch");
     if (A.ea.Wcols) {

@@ -217,6 +217,41 @@ __device__ __forceinline__ double kbuf_get(const SubMeta &M, const char *ws, int
     return M.kf32 ? (double)((const float *)(ws + M.offK))[idx] : ((const double *)(ws + M.offK))[idx];
 }
 
+// sum over a wave, the same in every lane
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// One wave writes the transpose of the 64 x 64 block at (r0, c0) of a 16-bit
+// matrix to (c0, r0): 8 x 8 blocks turned in registers, 128-byte row segments
+// both ways.
+__device__ __forceinline__ void mirror_block(uint16_t *X, int ldx, int r0, int c0) {
+    const int l = threadIdx.x & 63;
+    r0 += (l >> 3) * 8;
+    c0 += (l & 7) * 8;
+    uint4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = *(const uint4 *)(X + (int64_t)(r0 + q) * ldx + c0);
+    auto dw = [](const uint4 &x, int d) { return d == 0 ? x.x : d == 1 ? x.y : d == 2 ? x.z : x.w; };
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        uint32_t o[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t a = dw(v[2 * d], p >> 1), c = dw(v[2 * d + 1], p >> 1);
+            o[d] = (p & 1) ? ((a >> 16) | (c & 0xFFFF0000u)) : ((a & 0xFFFFu) | (c << 16));
+        }
+        *(uint4 *)(X + (int64_t)(c0 + p) * ldx + r0) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+// the symmetric 16-bit iteration stores this slot's iterates by their upper
+// 128 x 128 tiles (with 64-row tiles, whole)
+__device__ __forceinline__ bool upper_tiles(const SubMeta &M) {
+    return (int64_t)M.ntile_ns * 4096 != (int64_t)M.ldx * M.ldx;
+}
+
 // deterministic block reductions (256 threads); `red` is LDS scratch of 256
 __device__ __forceinline__ double block_sum(double v, double *red) {
     const int t = threadIdx.x;

@@ -21,12 +21,6 @@
 enum { IM_R = 1, IM_UPD = 2, IM_SQ = 3, IM_A = 4 };
 enum { IACT_STOP = 0, IACT_UPDATE = 1 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // c = 1 / max row sum of |S_J| over the padded np x np matrix (padding rows
 // are identity), Y_0 = c S_J and Z_0 = I in 16 bits; one workgroup per slot.
 template <typename T>

@@ -19,17 +19,27 @@
 
 enum { ACT_STOP = 0, ACT_UPDATE = 1, ACT_RESTART = 2 };
 
-// Decision of mode 2 at iteration `it`. Computed by thread 0 of every
+// Decision of mode 2 at iteration `it`. Computed by wave 0 of every
 // workgroup of the submatrix from data that is final before this launch
 // (the residual partials of mode 1 and rhist[0..it-1]); the tile-0
-// workgroup records it.
-__device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const char *ws, int it,
-                         int tile) {
+// workgroup records it. More than a few partials are read side by side: one
+// thread's chain of 25 additions took about 1.5 us of a tile.
+__device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const char *ws, int it, int tile,
+                         bool done) {
     const double *res = (const double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
     double ssum = 0.0;
-    for (int i = 0; i < M.ntile_ns; ++i) ssum += res[i];
-    const double r = sqrt(ssum);
+    if (M.ntile_ns <= 9) {
+        for (int i = 0; i < M.ntile_ns; ++i) ssum += res[i];
+    } else {
+        for (int i = threadIdx.x; i < M.ntile_ns; i += 64) ssum += res[i];
+        ssum = wave_sum(ssum);
+    }
     const double rprev = it > 0 ? ctl->rhist[it - 1] : INFINITY;
+    const int ra = ctl->restart_at;
+    // the reads above go out beside the one of `done`, not behind it
+    asm volatile("" ::"v"(ssum), "v"(rprev), "v"(ra));
+    if (done) return ACT_STOP;
+    const double r = sqrt(ssum);
     bool stop;
     if (na.fixed_iters > 0)
         stop = it >= na.fixed_iters;
@@ -43,7 +53,6 @@ __device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const 
     // restart_at may already hold it + 1 from the tile-0 workgroup)
     const bool forced = na.force_stall >= 0 && M.J == na.force_stall && it == NOLSM_STALL_IT;
     const bool diverge = forced || !isfinite(r) || (it >= 1 && r > 2.0 * rprev && r > 1.0);
-    const int ra = ctl->restart_at;
     int act;
     bool noconv = false;
     if (diverge && na.allow_restart && (ra < 0 || ra == it + 1)) {
@@ -59,7 +68,7 @@ __device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const 
     } else {
         act = ACT_UPDATE;
     }
-    if (tile == 0) {
+    if (tile == 0 && threadIdx.x == 0) {
         ctl->rhist[it] = r;
         if (act == ACT_STOP) {
             ctl->iters = it;
@@ -147,7 +156,11 @@ __device__ __forceinline__ void ns64_tile(const ChunkDev &cd, uint32_t task, cha
     T *Xn = (T *)(ws + ((it & 1) ? M.offX0 : M.offX1));
     T *Bb = (T *)(ws + M.offB);
     // one thread reads the control state and decides for the whole workgroup
-    if (threadIdx.x == 0) act_s = ctl->done ? ACT_STOP : (mode == 2 ? ns_decide(na, M, ctl, ws, it, tile) : ACT_UPDATE);
+    if (threadIdx.x < 64) {
+        const bool done = ctl->done != 0;
+        const int act = mode == 2 ? ns_decide(na, M, ctl, ws, it, tile, done) : (done ? ACT_STOP : ACT_UPDATE);
+        if (threadIdx.x == 0) act_s = act;
+    }
     __syncthreads();
     {
         const int act = act_s;
@@ -240,123 +253,157 @@ __global__ __launch_bounds__(256) void k_ns64_pq(ChunkDev cd, int ntask, int *q,
 }
 
 // ------------------------------------------------------------ FP16 / BF16
-// Symmetric sign iteration: the output tile (16-bit values) is staged
-// transposed in the operand LDS of lp_tile_product (free once it returns):
-// BM rows of BM values, 16-byte chunks swizzled by row, entry (r, c) of the
-// tile at row c, column r. Each lane holds 4 consecutive rows of one column
-// per group of 4 accumulator elements: one 8-byte store each.
-template <int BM> __device__ __forceinline__ int sym_idx(int row, int col) {
-    return row * BM + ((((col >> 3) ^ row ^ (row >> 3)) & (BM / 8 - 1)) << 3) + (col & 7);
+// 16 bytes, past the caches (nt) where an output is read again only a whole
+// pass over a large chunk later: kept out of L2 it does not displace the
+// operand tiles that the workgroups beside it share
+__device__ __forceinline__ void store16(uint16_t *p, const uint4 &v, bool nt) {
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    const v4u x = {v.x, v.y, v.z, v.w};
+    if (nt) __builtin_nontemporal_store(x, (v4u *)p);
+    else *(v4u *)p = x;
 }
-template <int BM, typename Val> __device__ __forceinline__ void sym_stage(Val val) {
-    constexpr int WT = BM / 2, NB = WT / 32;
-    uint16_t *st = lp_lds<BM>();
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int rl = wm * WT + i * 32 + q * 8 + (l >> 5) * 4, cl = wn * WT + j * 32 + (l & 31);
-                const uint32_t lo = (uint32_t)val(i, j, 4 * q) | ((uint32_t)val(i, j, 4 * q + 1) << 16);
-                const uint32_t hi = (uint32_t)val(i, j, 4 * q + 2) | ((uint32_t)val(i, j, 4 * q + 3) << 16);
-                *(uint2 *)(st + sym_idx<BM>(cl, rl)) = make_uint2(lo, hi);
-            }
-}
-// off-diagonal tile (ti, tj): its transpose goes to tile (tj, ti), 16-byte
-// row stores from the staged copy
-template <int BM> __device__ __forceinline__ void sym_store_mirror(uint16_t *X, int ldx, int row0, int col0) {
+// Output tile (ti, tj) of the symmetric iteration from its LDS copy
+// (tile_idx), 16-byte row stores of the rows and columns below np. A
+// diagonal tile is written exactly symmetric, from its upper triangle: X R
+// is symmetric only in exact arithmetic, and an iteration whose B operand is
+// read as rows (X^T) doubles the skew part that anticommutes with the sign
+// at every step.
+template <int BM> __device__ __forceinline__ void sym_store(uint16_t *X, int ldx, int np, int ti, int tj, bool nt) {
     constexpr int NCH = BM / 8;
     const uint16_t *st = lp_lds<BM>();
-    for (int f = threadIdx.x; f < BM * NCH; f += 256) {
-        const int cl = f / NCH, ch = f % NCH;
-        *(uint4 *)(X + (int64_t)(col0 + cl) * ldx + row0 + ch * 8) = *(const uint4 *)(st + sym_idx<BM>(cl, ch * 8));
-    }
-}
-// off-diagonal tile (ti, tj) itself from the staged copy of its transpose:
-// each thread reads an 8 x 8 block (eight 16-byte reads of copy rows),
-// transposes it in registers and writes eight 16-byte row segments, so the
-// 16 threads of a block row store 256 contiguous bytes of each tile row
-// (the row ^ (row >> 3) term of sym_idx spreads the eight copy rows a
-// block read touches, 8 apart, over all chunk positions)
-template <int BM> __device__ __forceinline__ void sym_store_direct(uint16_t *X, int ldx, int row0, int col0) {
-    constexpr int NB8 = BM / 8;
-    const uint16_t *st = lp_lds<BM>();
-    for (int b = threadIdx.x; b < NB8 * NB8; b += 256) {
-        const int r0 = (b / NB8) * 8, c0 = (b % NB8) * 8;
-        uint4 v[8];   // v[q] = T[r0 .. r0 + 7][c0 + q]
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = *(const uint4 *)(st + sym_idx<BM>(c0 + q, r0));
-        auto dw = [](const uint4 &x, int d) { return d == 0 ? x.x : d == 1 ? x.y : d == 2 ? x.z : x.w; };
-#pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            uint32_t o[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const uint32_t a = dw(v[2 * d], p >> 1), c = dw(v[2 * d + 1], p >> 1);
-                o[d] = (p & 1) ? ((a >> 16) | (c & 0xFFFF0000u)) : ((a & 0xFFFFu) | (c << 16));
-            }
-            *(uint4 *)(X + (int64_t)(row0 + r0 + p) * ldx + col0 + c0) = make_uint4(o[0], o[1], o[2], o[3]);
-        }
-    }
-}
-// A BM x BM tile of X_k into LDS as it stands (16-byte row loads), the
-// 16-byte chunk c of row r at chunk position c ^ 4 ((r / 4) % (BM / 32)):
-// the accumulator-layout reads (32 consecutive columns of one row, and of
-// the row 4 below) then fall on distinct banks
-template <int BM> __device__ __forceinline__ int dir_idx(int r, int c) {
-    return r * BM + ((((c >> 3) ^ (((r >> 2) & (BM / 32 - 1)) << 2))) << 3) + (c & 7);
-}
-template <int BM> __device__ __forceinline__ void dir_load(const uint16_t *X, int ldx, int row0, int col0) {
-    constexpr int NCH = BM / 8, NQ = BM * NCH / 256;
-    uint16_t *st = lp_lds<BM>();
-    uint4 v[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int f = threadIdx.x + q * 256, r = f / NCH, ch = f % NCH;
-        v[q] = *(const uint4 *)(X + (int64_t)(row0 + r) * ldx + col0 + ch * 8);
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int f = threadIdx.x + q * 256, r = f / NCH, ch = f % NCH;
-        *(uint4 *)(st + dir_idx<BM>(r, ch * 8)) = v[q];
-    }
-}
-// diagonal tile: X R (and X X^T up to rounding) is symmetric only in exact
-// arithmetic, and an iteration whose B operand is read as rows (X^T) doubles
-// the skew part that anticommutes with the sign at every step. The tile is
-// written exactly symmetric, from its upper triangle: (r, c) takes T[r][c]
-// for r <= c and T[c][r] below (staged copy: T[r][c] at row c, column r).
-template <int BM> __device__ __forceinline__ void sym_store_diag(uint16_t *X, int ldx, int row0) {
-    constexpr int NCH = BM / 8;
-    const uint16_t *st = lp_lds<BM>();
+    const int row0 = ti * BM, col0 = tj * BM;
+    // eight values from a function of their position
+    auto pack = [](auto at) {
+        return make_uint4((uint32_t)at(0) | ((uint32_t)at(1) << 16), (uint32_t)at(2) | ((uint32_t)at(3) << 16),
+                          (uint32_t)at(4) | ((uint32_t)at(5) << 16), (uint32_t)at(6) | ((uint32_t)at(7) << 16));
+    };
+#pragma unroll 4
     for (int f = threadIdx.x; f < BM * NCH; f += 256) {
         const int r = f / NCH, c0 = (f % NCH) * 8;
+        if (row0 + r >= np || col0 + c0 >= np) continue;
         uint4 v;
-        if (c0 + 7 < r) {
-            v = *(const uint4 *)(st + sym_idx<BM>(r, c0));   // T[c][r], c < r: row r of the copy
-        } else {
-            uint16_t h[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int c = c0 + k;
-                h[k] = (r <= c) ? st[sym_idx<BM>(c, r)] : st[sym_idx<BM>(r, c)];
-            }
-            v = make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16), h[4] | ((uint32_t)h[5] << 16),
-                           h[6] | ((uint32_t)h[7] << 16));
-        }
-        *(uint4 *)(X + (int64_t)(row0 + r) * ldx + row0 + c0) = v;
+        if (ti != tj || c0 >= r)
+            v = *(const uint4 *)(st + tile_idx<BM>(r, c0));
+        else
+            v = pack([&](int k) { return st[tile_idx<BM>(min(r, c0 + k), max(r, c0 + k))]; });
+        store16(X + (int64_t)(row0 + r) * ldx + col0 + c0, v, nt);
+        if (BM == 64 && ti != tj)   // both triangles are stored: row r of the transpose
+            store16(X + (int64_t)(col0 + r) * ldx + row0 + c0, pack([&](int k) { return st[tile_idx<BM>(c0 + k, r)]; }),
+                    nt);
     }
+}
+
+// One upper BM x BM tile of the symmetric sign iteration (modes as below).
+// With 128-row tiles X_k and R are stored by their upper tiles, and so are
+// the results. What is left below the diagonal tiles is never read until it
+// is filled in for the returned iterate.
+template <typename T, int BM>
+__device__ __forceinline__ void ns_sym_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
+                                            int mode) {
+    __shared__ double red[4];
+    __shared__ int act_s;
+    if (task == NOLSM_TASK_NONE) return;
+    const int s = task_slot(task), ti = task_a(task), tj = task_b(task);
+    const SubMeta M = cd.meta[s];
+    SubCtl *ctl = cd.ctl + s;
+    const int np = M.np, ldx = M.ldx, nt = (np + BM - 1) / BM, tile = ti * nt + tj;
+    uint16_t *Xc = (uint16_t *)(ws + ((it & 1) ? M.offX1 : M.offX0));
+    uint16_t *Xn = (uint16_t *)(ws + ((it & 1) ? M.offX0 : M.offX1));
+    uint16_t *Bb = (uint16_t *)(ws + M.offB);
+    // a converged submatrix costs one read. In mode 2 another workgroup may
+    // record this iteration's stop meanwhile: whichever wave sees it loads
+    // nothing, and `begin` comes to the same stop for all of them.
+    const bool done = __builtin_amdgcn_readfirstlane(*(volatile int32_t *)&ctl->done) != 0;
+    if (done && mode == 1) return;
+    // wave 0 reads the control state and decides for the whole workgroup
+    auto begin = [&]() {
+        if (mode == 1) return true;
+        if (threadIdx.x < 64) {
+            const int act = ns_decide(na, M, ctl, ws, it, tile, done);
+            if (threadIdx.x == 0) act_s = act;
+        }
+        __syncthreads();
+        if (act_s == ACT_RESTART) {
+            auto enc = [](double v) { return Lp<T>::enc((float)v); };
+            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, enc, true);
+            if (BM == 64 && ti != tj) restart_tile(M, ctl, ws, Xn, tj * BM, ti * BM, BM, BM, enc, true);
+        }
+        return act_s == ACT_UPDATE;
+    };
+    constexpr int WT = BM / 2, NB = WT / 32;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w >> 1, wn = w & 1;
+    uint16_t *st = lp_lds<BM>();
+    const int rl = wm * WT + (l & 31), cl = wn * WT + (l >> 5) * 4;
+    double part = 0.0;
+    auto finish = [&](v16f(&acc)[NB][NB]) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int r = rl + i * 32, c = cl + j * 32 + q * 8;
+                    uint2 *p = (uint2 *)(st + tile_idx<BM>(r, c));
+                    float v[4];
+                    if (mode == 1) {
+                        // R = I - X^2 is small near convergence and keeps full
+                        // relative precision in 16 bits (3I - X^2 would not: its
+                        // diagonal ~2 is quantised at 2^-9 in FP16)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            v[e] = ((ti == tj && r == c + e) ? 1.0f : 0.0f) - acc[i][j][4 * q + e];
+                            part += (double)v[e] * (double)v[e];
+                        }
+                    } else {
+                        // X_{k+1} = X_k + X_k R / 2 = X_k (3I - X_k^2) / 2, X_k
+                        // from LDS, the result in its place
+                        const uint2 x = *p;
+                        const uint16_t h[4] = {(uint16_t)x.x, (uint16_t)(x.x >> 16), (uint16_t)x.y, (uint16_t)(x.y >> 16)};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = Lp<T>::dec(h[e]) + 0.5f * acc[i][j][4 * q + e];
+                    }
+                    *p = make_uint2((uint32_t)Lp<T>::enc(v[0]) | ((uint32_t)Lp<T>::enc(v[1]) << 16),
+                                    (uint32_t)Lp<T>::enc(v[2]) | ((uint32_t)Lp<T>::enc(v[3]) << 16));
+                }
+    };
+    if (!lp_sym_product<T, BM>(Xc, mode == 1 ? Xc : Bb, mode == 1 ? nullptr : Xc, ldx, np, ti, tj, !done, begin,
+                               finish))
+        return;
+    if (mode == 1) {
+        // a value off the diagonal counts for its mirror too
+        part = wave_sum(part) * ((ti != tj || wm < wn) ? 2.0 : 1.0);
+        if (l == 0) red[w] = part;
+    }
+    __syncthreads();
+    if (mode == 1 && threadIdx.x == 0) {
+        double *res = (double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
+        res[tile] = (red[0] + red[1]) + (red[2] + red[3]);
+        if (ti != tj) res[tj * nt + ti] = 0.0;   // the mirror tile is never launched
+    }
+    sym_store<BM>(mode == 1 ? Bb : Xn, ldx, np, ti, tj, na.nt_out);
+}
+
+// Fills in the tiles below the diagonal of the returned iterate, which the
+// finishing products read by rows: tile (tj, ti) is the transpose of the
+// stored tile (ti, tj). One pass over the matrix, against one saved in every
+// half-iteration by not storing them.
+__global__ __launch_bounds__(256) void k_ns_mirror(ChunkDev cd, char *ws) {
+    const uint32_t task = xcd_task(cd.t_ns);   // 128-row tiles
+    if (task == NOLSM_TASK_NONE) return;
+    const int s = task_slot(task), ti = task_a(task), tj = task_b(task);
+    if (ti == tj) return;
+    const SubMeta M = cd.meta[s];
+    const SubCtl *ctl = cd.ctl + s;
+    if (ctl->status == NOLSM_MOL_NOT_SPD) return;
+    const int w = threadIdx.x >> 6, r0 = ti * 128 + (w >> 1) * 64, c0 = tj * 128 + (w & 1) * 64;
+    if (c0 >= M.np) return;   // ti < tj: r0 is below np
+    mirror_block((uint16_t *)(ws + ((ctl->iters & 1) ? M.offX1 : M.offX0)), M.ldx, r0, c0);
 }
 
 // One BM x BM tile of a sign-iteration GEMM: mode 1 forms R = I - X_k^2 and
 // the tile's share of ||R||_F^2, mode 2 decides stop / continue / restart and
-// forms X_{k+1} = X_k + X_k R / 2. SYM: X_k and R are symmetric, only tiles
-// ti <= tj are launched and each writes its mirror too.
-// DIAG1: the diagonal tiles of X_k^2 take the one-operand product (kept out
-// of the persistent kernel, whose loop would spill with both copies inlined)
-template <typename T, int BM, bool SYM, bool DIAG1 = false>
+// forms X_{k+1} = X_k + X_k R / 2.
+template <typename T, int BM>
 __device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
                                            int mode) {
     __shared__ double red[256];
@@ -370,17 +417,17 @@ __device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, ch
     uint16_t *Xn = (uint16_t *)(ws + ((it & 1) ? M.offX0 : M.offX1));
     uint16_t *Bb = (uint16_t *)(ws + M.offB);
     // one thread reads the control state and decides for the whole workgroup
-    if (threadIdx.x == 0) act_s = ctl->done ? ACT_STOP : (mode == 2 ? ns_decide(na, M, ctl, ws, it, tile) : ACT_UPDATE);
+    if (threadIdx.x < 64) {
+        const bool done = ctl->done != 0;
+        const int act = mode == 2 ? ns_decide(na, M, ctl, ws, it, tile, done) : (done ? ACT_STOP : ACT_UPDATE);
+        if (threadIdx.x == 0) act_s = act;
+    }
     __syncthreads();
     {
         const int act = act_s;
         if (act == ACT_STOP) return;
         if (act == ACT_RESTART) {
-            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, [](double v) { return Lp<T>::enc((float)v); },
-                         SYM);
-            if (SYM && ti != tj)
-                restart_tile(M, ctl, ws, Xn, tj * BM, ti * BM, BM, BM, [](double v) { return Lp<T>::enc((float)v); },
-                             SYM);
+            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, [](double v) { return Lp<T>::enc((float)v); });
             return;
         }
     }
@@ -389,9 +436,7 @@ __device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, ch
     const int row0 = ti * BM, col0 = tj * BM, ldx = M.ldx;
     const int nrec = ldx * ldx * 2;
     v16f acc[NB][NB];
-    // a diagonal tile of X_k^2 (symmetric route) loads its one operand tile once
-    if (DIAG1 && SYM && mode == 1 && ti == tj) lp_tile_product<T, BM, SYM, DIAG1 && SYM>(Xc, Xc, ldx, np, row0, col0, acc);
-    else lp_tile_product<T, BM, SYM>(Xc, (mode == 1) ? Xc : Bb, ldx, np, row0, col0, acc);
+    lp_tile_product<T, BM>(Xc, (mode == 1) ? Xc : Bb, ldx, np, row0, col0, acc);
     // Epilogue over the whole tile, padding included: rows and columns in
     // [np, ldx) of R and X_{k+1} only ever feed outputs that are never used,
     // so the accesses need no bounds test and the X_k reads of the update
@@ -401,58 +446,7 @@ __device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, ch
     const int er0 = row0 + wm * WT + (l >> 5) * 4, ec0 = col0 + wn * WT + (l & 31);
     const uint32_t eo = (uint32_t)((er0 * ldx + ec0) * 2);
 #define NS_EOFF(i, j, e) ((((i) * 32 + ((e) >> 2) * 8 + ((e) & 3)) * ldx + (j) * 32) * 2)
-    if constexpr (SYM) {
-        // every value is formed first and staged in LDS behind one barrier,
-        // and all global stores come after it: a barrier behind stores
-        // would wait for them to complete
-        uint16_t *Out;
-        if (mode == 1) {
-            double part = 0.0;
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int gr = er0 + i * 32 + (e >> 2) * 8 + (e & 3), gc = ec0 + j * 32;
-                        acc[i][j][e] = (gr == gc ? 1.0f : 0.0f) - acc[i][j][e];   // R
-                        if (gr < np && gc < np) part += (double)acc[i][j][e] * (double)acc[i][j][e];
-                    }
-            const double sum = block_sum(part, red);
-            if (threadIdx.x == 0) {
-                double *res = (double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
-                res[tile] = (ti != tj ? 2.0 : 1.0) * sum;   // the mirror tile is never launched
-                if (ti != tj) res[tj * nt + ti] = 0.0;
-            }
-            Out = Bb;
-        } else {
-            // X_k of the tile through LDS (the operand buffers are free
-            // again): 16-byte row loads, then each lane's elements
-            dir_load<BM>(Xc, ldx, row0, col0);
-            __syncthreads();
-            const uint16_t *xs = lp_lds<BM>();
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int rl = wm * WT + i * 32 + (e >> 2) * 8 + (l >> 5) * 4 + (e & 3);
-                        const int cl = wn * WT + j * 32 + (l & 31);
-                        acc[i][j][e] = Lp<T>::dec(xs[dir_idx<BM>(rl, cl)]) + 0.5f * acc[i][j][e];
-                    }
-            __syncthreads();
-            Out = Xn;
-        }
-        sym_stage<BM>([&](int i, int j, int e) { return Lp<T>::enc(acc[i][j][e]); });
-        __syncthreads();
-        if (ti != tj) {
-            sym_store_direct<BM>(Out, ldx, row0, col0);
-            sym_store_mirror<BM>(Out, ldx, row0, col0);
-        } else {
-            sym_store_diag<BM>(Out, ldx, row0);
-        }
-    } else if (mode == 1) {
+    if (mode == 1) {
         const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc((void *)Bb, (short)0, nrec, 0x00020000);
         double part = 0.0;
 #pragma unroll
@@ -493,9 +487,16 @@ __device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, ch
 }
 
 template <typename T, int BM, bool SYM>
+__device__ __forceinline__ void ns_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
+                                        int mode) {
+    if constexpr (SYM) ns_sym_tile<T, BM>(cd, task, ws, na, it, mode);
+    else ns_lp_tile<T, BM>(cd, task, ws, na, it, mode);
+}
+
+template <typename T, int BM, bool SYM>
 __global__ __launch_bounds__(256, 3) void k_ns_lp(ChunkDev cd, const uint32_t *tasks, char *ws, NsArgs na, int it,
                                                int mode) {
-    ns_lp_tile<T, BM, SYM, true>(cd, xcd_task(tasks), ws, na, it, mode);
+    ns_tile<T, BM, SYM>(cd, xcd_task(tasks), ws, na, it, mode);
 }
 
 template <typename T, int BM, bool SYM>
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(256, 3) void k_ns_lp_pq(ChunkDev cd, const uint32_t
     for (;;) {
         const int i = queue_pop(q + x, &idx_s);
         if (i >= seg) break;
-        ns_lp_tile<T, BM, SYM>(cd, tasks[x * seg + i], ws, na, it, mode);
+        ns_tile<T, BM, SYM>(cd, tasks[x * seg + i], ws, na, it, mode);
     }
 }
 
@@ -533,7 +534,10 @@ __global__ __launch_bounds__(256, 2) void k_ns_lp_tail(ChunkDev cd, const uint32
         }
         __syncthreads();
         const int nk = nkept;
-        for (int k = 0; k < nk; ++k) ns_lp_tile<T, BM, SYM>(cd, kept[k], ws, na, it, mode);
+        for (int k = 0; k < nk; ++k) {
+            ns_tile<T, BM, SYM>(cd, kept[k], ws, na, it, mode);
+            __syncthreads();   // its LDS is free again
+        }
         __syncthreads();
     }
 }
@@ -551,7 +555,10 @@ static int persistent_grid(const NsArgs &na, int ntask) {
 }
 
 template <typename T, bool SYM>
-static void launch_lp(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
+static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode, hipStream_t st) {
+    // more tiles than run at once (three workgroups per CU): their outputs
+    // leave the caches before the next launch reads them
+    na.nt_out = cd.n_ns > na.pgrid + na.pgrid / 2;
     if (na.persistent) {
         if (cd.n_ns > 0)
             hipLaunchKernelGGL((k_ns_lp_pq<T, 128, SYM>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd,
@@ -609,4 +616,10 @@ hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// symmetric route, after the last iteration: the returned iterates whole
+hipError_t launch_ns_mirror(const ChunkDev &cd, char *ws, hipStream_t st) {
+    if (cd.n_ns > 0) hipLaunchKernelGGL(k_ns_mirror, dim3(cd.n_ns), dim3(256), 0, st, cd, ws);
+    return hipGetLastError();
 }

@@ -41,6 +41,7 @@ struct NsArgs {
     int32_t persistent;    // queue-driven fixed grid instead of one workgroup per tile
     int32_t pgrid;         // workgroups of a persistent launch
     int32_t sym;           // symmetric sign iteration: upper tiles, mirrored (FP16/BF16)
+    int32_t nt_out;        // symmetric iteration: outputs stored past the caches (set per launch)
     int32_t force_stall;   // molecule taken as diverged at iteration NOLSM_STALL_IT (-1: none)
 };
 #define NOLSM_STALL_IT 2
@@ -59,7 +60,8 @@ struct FinishArgs {
     int32_t prec;
     int32_t nfinal;        // 0, 1, 2 column-restricted finishing iterations
     int32_t rows;          // FP16: the row-streaming kernel instead of the fused one
-    int32_t pad_;
+    int32_t mirror;        // the iterate is stored by its upper tiles: complete it
+                           // in the fused kernel
 };
 
 struct ExtractArgs {
@@ -94,6 +96,7 @@ hipError_t launch_trace_sums(const void *stats, int32_t nb, char *ws, hipStream_
 hipError_t launch_bounds(const ChunkDev &cd, char *ws, const BoundsArgs &ba, int prec, hipStream_t st);
 hipError_t launch_convert(const ChunkDev &cd, char *ws, int prec, int use_scale_g, int sym, hipStream_t st);
 hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it, hipStream_t st);
+hipError_t launch_ns_mirror(const ChunkDev &cd, char *ws, hipStream_t st);
 hipError_t launch_finish(const ChunkDev &cd, char *ws, const FinishArgs &fa, hipStream_t st);
 hipError_t launch_extract(const ChunkDev &cd, char *ws, const ExtractArgs &ea, hipStream_t st);
 hipError_t launch_assemble(const double *Dcols, double *Dval, const int32_t *scatter_pos, int64_t sum_m,
