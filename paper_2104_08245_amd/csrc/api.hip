@@ -76,6 +76,7 @@ static ChunkDev chunk_dev(const nolsm_plan *pl, const HostChunk &ch, char *ws) {
     cd.max_m = ch.max_m;
     cd.max_np = ch.max_np;
     cd.max_own = ch.max_own;
+    cd.ns_wide = ch.ns_wide ? 1 : 0;
     return cd;
 }
 

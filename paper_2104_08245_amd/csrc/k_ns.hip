@@ -124,38 +124,51 @@ template <> struct Mma16<float> {
     static __device__ __forceinline__ int row(int lk, int e) { return 4 * lk + e; }
 };
 
-template <typename T>
-__device__ __forceinline__ void g2s_t(T (*s)[LDP], const T *g, int64_t ld) {
-    const int t = threadIdx.x;
-    const int c4 = (t & 15) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = i * 16 + (t >> 4);
-        const T *p = g + (int64_t)r * ld + c4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[r][c4 + e] = p[e];
-    }
-}
+// LDS strides of the operand slices (64 x BK of A, BK x 32 NC of B), in
+// values: an A operand read touches 16 rows and 4 (FP32) or 2 (FP64, per
+// half-wave) neighbouring k, a B operand read 16 neighbouring columns of as
+// many k rows, and each falls on distinct banks; rows start 16-byte aligned
+template <typename T, int NC> struct Ns64Tile {
+    static constexpr int BK = NC == 4 ? 32 : 64;
+    static constexpr int LA = BK + (sizeof(T) == 8 ? 2 : 4), LB = 32 * NC + 16;
+};
 
-// One 64x64 output tile of one half-iteration (body shared by the
-// one-workgroup-per-tile launch and the persistent queue launch).
-template <typename T>
+// One 64 x 32 NC output tile of one half-iteration (body shared by the
+// one-workgroup-per-tile launch and the persistent queue launch): NC = 2, one
+// 64-column tile, or NC = 4, two of them, tj and tj + 1 (the second may be
+// past the matrix). The matrix cores bound it. With NC = 4 each wave holds
+// 32 x 64 as 2 x 4 blocks, whose eight chains of products keep a SIMD's
+// matrix core busy from two waves on (four chains a wave reached 125 of 155
+// TF/s in FP32 with four waves): 512 submatrices of about 612 rows in FP64
+// 4433 us a launch against 4834 with NC = 2 (5938 before the slices were
+// fetched ahead), 777 in FP32 3296 against 3716 (3850). NC = 2 serves chunks
+// too small to fill the GPU with the wider tiles (plan.cpp). The next slice
+// is fetched into registers while this one is multiplied from LDS. The
+// contraction stops at n (X_k and R are identity and zero on the padding,
+// whose products are exact zeros), and the padding of a result is set rather
+// than computed.
+template <typename T, int NC>
 __device__ __forceinline__ void ns64_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
                                           int mode) {
     typedef typename Mma16<T>::acc_t acc_t;
-    __shared__ T sA[64][LDP];
-    __shared__ T sB[64][LDP];
-    __shared__ double red[256];
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int BK = Ns64Tile<T, NC>::BK, LA = Ns64Tile<T, NC>::LA, LB = Ns64Tile<T, NC>::LB;
+    constexpr int BN = 32 * NC, VE = 16 / sizeof(T);
+    constexpr int AL = BK / VE, AR = 256 / AL, AP = 64 / AR;    // lanes per row, rows per pass, passes of A
+    constexpr int BL = BN / VE, BR = 256 / BL, BP = BK / BR;   // and of B
+    __shared__ __attribute__((aligned(16))) T sA[64 * LA];
+    __shared__ __attribute__((aligned(16))) T sB[BK * LB];
+    __shared__ double red[4];
     __shared__ int act_s;
     if (task == NOLSM_TASK_NONE) return;
     const int s = task_slot(task), ti = task_a(task), tj = task_b(task);
     const SubMeta M = cd.meta[s];
     SubCtl *ctl = cd.ctl + s;
-    const int np = M.np, nt = np / 64, tile = ti * nt + tj;
+    const int np = M.np, n = M.n, nt = np / 64, tile = ti * nt + tj;
     T *Xc = (T *)(ws + ((it & 1) ? M.offX1 : M.offX0));
     T *Xn = (T *)(ws + ((it & 1) ? M.offX0 : M.offX1));
     T *Bb = (T *)(ws + M.offB);
-    // one thread reads the control state and decides for the whole workgroup
+    // wave 0 reads the control state and decides for the whole workgroup
     if (threadIdx.x < 64) {
         const bool done = ctl->done != 0;
         const int act = mode == 2 ? ns_decide(na, M, ctl, ws, it, tile, done) : (done ? ACT_STOP : ACT_UPDATE);
@@ -166,61 +179,115 @@ __device__ __forceinline__ void ns64_tile(const ChunkDev &cd, uint32_t task, cha
         const int act = act_s;
         if (act == ACT_STOP) return;
         if (act == ACT_RESTART) {
-            restart_tile(M, ctl, ws, Xn, ti * 64, tj * 64, 64, 64, [](double v) { return (T)v; });
+            // columns past np are left alone
+            restart_tile(M, ctl, ws, Xn, ti * 64, tj * 64, 64, BN, [](double v) { return (T)v; });
             return;
         }
     }
     const T *Bop = (mode == 1) ? Xc : Bb;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
+    const int r0 = (w >> 1) * 32, c0 = (w & 1) * 16 * NC;
     const int li = l & 15, lk = l >> 4;
-    acc_t acc[2][2];
+    const int ar = t / AL, ac = (t % AL) * VE, br = t / BL, bc = (t % BL) * VE;
+    const T *Ag = Xc + (int64_t)(ti * 64 + ar) * np + ac, *Bg = Bop + (int64_t)br * np + tj * 64 + bc;
+    const bool bin = tj * 64 + bc < np;
+    const int nk = (n + BK - 1) / BK;
+    vec pa[AP], pb[BP];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int p = 0; p < BP; ++p) pb[p] = (vec)0;
+    auto fetch = [&](int kt) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (acc_t){0, 0, 0, 0};
-    for (int kt = 0; kt < nt; ++kt) {
-        g2s_t(sA, Xc + (int64_t)(ti * 64) * np + kt * 64, np);
-        g2s_t(sB, Bop + (int64_t)(kt * 64) * np + tj * 64, np);
-        __syncthreads();
-#pragma unroll 4
-        for (int k0 = 0; k0 < 64; k0 += 4) {
-            const int k = k0 + lk;
-            T a[2], b[2];
+        for (int p = 0; p < AP; ++p) pa[p] = *(const vec *)(Ag + (int64_t)p * AR * np + kt * BK);
+        if (bin)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = sA[r0 + i * 16 + li][k];
+            for (int p = 0; p < BP; ++p) pb[p] = *(const vec *)(Bg + (int64_t)(kt * BK + p * BR) * np);
+    };
+    auto stash = [&]() {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = sB[k][c0 + j * 16 + li];
+        for (int p = 0; p < AP; ++p) *(vec *)(sA + (ar + p * AR) * LA + ac) = pa[p];
+#pragma unroll
+        for (int p = 0; p < BP; ++p) *(vec *)(sB + (br + p * BR) * LB + bc) = pb[p];
+    };
+    double part = 0.0;
+    fetch(0);
+    stash();
+    __syncthreads();
+    if (tj * 64 + c0 >= np) {
+        // past the matrix: this wave only loads and stores for the others
+        for (int kt = 0; kt + 1 < nk; ++kt) {
+            fetch(kt + 1);
+            __syncthreads();
+            stash();
+            __syncthreads();
+        }
+    } else {
+        acc_t acc[2][NC];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) acc[i][j] = (acc_t){0, 0, 0, 0};
+        const T *ra = sA + (r0 + li) * LA + lk, *rb = sB + lk * LB + c0 + li;
+        auto step = [&](int k) {
+            T a[2], b[NC];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = ra[i * 16 * LA + 4 * k];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) b[j] = rb[4 * k * LB + j * 16];
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = Mma16<T>::mma(a[i], b[j], acc[i][j]);
+                for (int j = 0; j < NC; ++j) acc[i][j] = Mma16<T>::mma(a[i], b[j], acc[i][j]);
+        };
+        for (int kt = 0; kt + 1 < nk; ++kt) {
+            fetch(kt + 1);
+            __builtin_amdgcn_sched_barrier(0);   // ahead of the products, not next to their use
+#pragma unroll
+            for (int k = 0; k < BK / 4; ++k) step(k);
+            __syncthreads();
+            stash();
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    double part = 0.0;
+        const int ks = (n - (nk - 1) * BK + 3) / 4;   // the last slice, to n
+        for (int k = 0; k < ks; ++k) step(k);
+        const int gr0 = ti * 64 + r0, gc0 = tj * 64 + c0 + li;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+            T x[NC][4];
+            if (mode == 2)   // X_k of the block row, all loads before the stores
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < NC; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int gr = ti * 64 + r0 + i * 16 + Mma16<T>::row(lk, e);
-                const int gc = tj * 64 + c0 + j * 16 + li;
-                const T v = acc[i][j][e];
-                const int64_t o = (int64_t)gr * np + gc;
-                if (mode == 1) {
-                    // R = I - X^2; the update below is X + X R / 2 = X (3I - X^2) / 2
-                    const T rr = (gr == gc ? (T)1 : (T)0) - v;
-                    part += (double)rr * (double)rr;
-                    Bb[o] = rr;
-                } else {
-                    Xn[o] = Xc[o] + (T)0.5 * v;
+                    for (int e = 0; e < 4; ++e)
+                        x[j][e] = Xc[(int64_t)(gr0 + i * 16 + Mma16<T>::row(lk, e)) * np + gc0 + j * 16];
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int gr = gr0 + i * 16 + Mma16<T>::row(lk, e);
+                    const int gc = gc0 + j * 16;
+                    const bool pad = gr >= n || gc >= n;
+                    const T v = acc[i][j][e];
+                    const int64_t o = (int64_t)gr * np + gc;
+                    if (mode == 1) {
+                        // R = I - X^2; the update below is X + X R / 2 = X (3I - X^2) / 2
+                        const T rr = pad ? (T)0 : (gr == gc ? (T)1 : (T)0) - v;
+                        part += (double)rr * (double)rr;
+                        Bb[o] = rr;
+                    } else {
+                        Xn[o] = pad ? x[j][e] : x[j][e] + (T)0.5 * v;
+                    }
                 }
-            }
+        }
+    }
     if (mode == 1) {
-        const double sum = block_sum(part, red);
-        if (threadIdx.x == 0) ((double *)(ws + M.offRes))[(int64_t)it * M.ntile_ns + tile] = sum;
+        part = wave_sum(part);
+        if (l == 0) red[w] = part;
+        __syncthreads();
+        if (t == 0) {
+            double *res = (double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
+            res[tile] = (red[0] + red[1]) + (red[2] + red[3]);
+            if (NC == 4 && tj + 1 < nt) res[tile + 1] = 0.0;
+        }
     }
 }
 
@@ -235,20 +302,56 @@ __device__ __forceinline__ int queue_pop(int *q, int *slot) {
     return *slot;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_ns64(ChunkDev cd, char *ws, NsArgs na, int it, int mode) {
-    ns64_tile<T>(cd, xcd_task(cd.t_ns), ws, na, it, mode);
+template <typename T, int NC>
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64(ChunkDev cd, char *ws, NsArgs na, int it,
+                                                                    int mode) {
+    ns64_tile<T, NC>(cd, xcd_task(cd.t_ns), ws, na, it, mode);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_ns64_pq(ChunkDev cd, int ntask, int *q, char *ws, NsArgs na, int it,
-                                                 int mode) {
+// Late iterations, when most submatrices have converged: a small grid in
+// which every workgroup scans its share of its XCD's task segment, 256
+// tasks at a time (one per thread), keeps the tasks whose submatrix is still
+// iterating and runs those tiles. A launch after convergence then costs one
+// scan instead of one dispatched workgroup per tile. The order in which the
+// kept tiles run does not matter: each writes only its own outputs.
+template <typename Run>
+__device__ __forceinline__ void scan_tasks(const ChunkDev &cd, const uint32_t *tasks, int ntask, Run run) {
+    __shared__ uint32_t kept[256];
+    __shared__ int nkept;
+    const int x = blockIdx.x & 7, seg = ntask >> 3, g8 = gridDim.x >> 3, wb = blockIdx.x >> 3;
+    const int span = (seg + g8 - 1) / g8, lo = wb * span, hi = min(seg, lo + span);
+    for (int i0 = lo; i0 < hi; i0 += 256) {
+        if (threadIdx.x == 0) nkept = 0;
+        __syncthreads();
+        const int i = i0 + (int)threadIdx.x;
+        if (i < hi) {
+            const uint32_t task = tasks[x * seg + i];
+            if (task != NOLSM_TASK_NONE && !cd.ctl[task_slot(task)].done) kept[atomicAdd(&nkept, 1)] = task;
+        }
+        __syncthreads();
+        const int nk = nkept;
+        for (int k = 0; k < nk; ++k) {
+            run(kept[k]);
+            __syncthreads();   // its LDS is free again
+        }
+        __syncthreads();
+    }
+}
+
+template <typename T, int NC>
+__global__ __launch_bounds__(256, 2) void k_ns64_tail(ChunkDev cd, char *ws, NsArgs na, int it, int mode) {
+    scan_tasks(cd, cd.t_ns, cd.n_ns, [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
+}
+
+template <typename T, int NC>
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64_pq(ChunkDev cd, int ntask, int *q, char *ws,
+                                                                       NsArgs na, int it, int mode) {
     __shared__ int idx_s;
     const int x = blockIdx.x & 7, seg = ntask >> 3;
     for (;;) {
         const int i = queue_pop(q + x, &idx_s);
         if (i >= seg) break;
-        ns64_tile<T>(cd, cd.t_ns[x * seg + i], ws, na, it, mode);
+        ns64_tile<T, NC>(cd, cd.t_ns[x * seg + i], ws, na, it, mode);
     }
 }
 
@@ -511,38 +614,21 @@ __global__ __launch_bounds__(256, 3) void k_ns_lp_pq(ChunkDev cd, const uint32_t
     }
 }
 
-// Late iterations, when most submatrices have converged: a small grid in
-// which every workgroup scans its share of its XCD's task segment, 256
-// tasks at a time (one per thread), keeps the tasks whose submatrix is still
-// iterating and runs those tiles. A launch after convergence then costs one
-// scan instead of one dispatched workgroup per tile. The order in which the
-// kept tiles run does not matter: each writes only its own outputs.
 template <typename T, int BM, bool SYM>
 __global__ __launch_bounds__(256, 2) void k_ns_lp_tail(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws,
                                                     NsArgs na, int it, int mode) {
-    __shared__ uint32_t kept[256];
-    __shared__ int nkept;
-    const int x = blockIdx.x & 7, seg = ntask >> 3, g8 = gridDim.x >> 3, wb = blockIdx.x >> 3;
-    const int span = (seg + g8 - 1) / g8, lo = wb * span, hi = min(seg, lo + span);
-    for (int i0 = lo; i0 < hi; i0 += 256) {
-        if (threadIdx.x == 0) nkept = 0;
-        __syncthreads();
-        const int i = i0 + (int)threadIdx.x;
-        if (i < hi) {
-            const uint32_t task = tasks[x * seg + i];
-            if (task != NOLSM_TASK_NONE && !cd.ctl[task_slot(task)].done) kept[atomicAdd(&nkept, 1)] = task;
-        }
-        __syncthreads();
-        const int nk = nkept;
-        for (int k = 0; k < nk; ++k) {
-            ns_tile<T, BM, SYM>(cd, kept[k], ws, na, it, mode);
-            __syncthreads();   // its LDS is free again
-        }
-        __syncthreads();
-    }
+    scan_tasks(cd, tasks, ntask, [&](uint32_t task) { ns_tile<T, BM, SYM>(cd, task, ws, na, it, mode); });
 }
-// iterations from this one on take the scanning launch
+// iterations from this one on take the scanning launch (FP64 / FP32, which
+// iterate longer: from the second one on; 64 launches after convergence then
+// take 4 us each instead of 75 on 512 submatrices of about 612 rows)
 #define NS_TAIL_IT 16
+#define NS64_TAIL_IT 18
+// its grid: four scanning workgroups per CU (2 x pgrid), at most one per task
+static int scan_grid(const NsArgs &na, int ntask) {
+    const int g = (2 * na.pgrid < ntask ? 2 * na.pgrid : ntask) / 8 * 8;
+    return g < 8 ? 8 : g;
+}
 
 // queue counters of one launch: [iteration][half][tile class][XCD]
 static int *launch_queue(const ChunkDev &cd, int it, int mode, int cls) {
@@ -569,16 +655,11 @@ static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode,
         return;
     }
     if (it >= NS_TAIL_IT) {
-        // four scanning workgroups per CU (2 x pgrid), at most one per task
-        auto grid = [&](int ntask) {
-            const int g = (2 * na.pgrid < ntask ? 2 * na.pgrid : ntask) / 8 * 8;
-            return g < 8 ? 8 : g;
-        };
         if (cd.n_ns > 0)
-            hipLaunchKernelGGL((k_ns_lp_tail<T, 128, SYM>), dim3(grid(cd.n_ns)), dim3(256), 0, st, cd, cd.t_ns,
+            hipLaunchKernelGGL((k_ns_lp_tail<T, 128, SYM>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.t_ns,
                                cd.n_ns, ws, na, it, mode);
         if (cd.n_ns64 > 0)
-            hipLaunchKernelGGL((k_ns_lp_tail<T, 64, SYM>), dim3(grid(cd.n_ns64)), dim3(256), 0, st, cd, cd.t_ns64,
+            hipLaunchKernelGGL((k_ns_lp_tail<T, 64, SYM>), dim3(scan_grid(na, cd.n_ns64)), dim3(256), 0, st, cd, cd.t_ns64,
                                cd.n_ns64, ws, na, it, mode);
         return;
     }
@@ -588,14 +669,21 @@ static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode,
         hipLaunchKernelGGL((k_ns_lp<T, 64, SYM>), dim3(cd.n_ns64), dim3(256), 0, st, cd, cd.t_ns64, ws, na, it, mode);
 }
 
+template <typename T, int NC>
+static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
+    if (na.persistent)
+        hipLaunchKernelGGL((k_ns64_pq<T, NC>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.n_ns,
+                           launch_queue(cd, it, mode, 0), ws, na, it, mode);
+    else if (it >= NS64_TAIL_IT)
+        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
+    else
+        hipLaunchKernelGGL((k_ns64<T, NC>), dim3(cd.n_ns), dim3(256), 0, st, cd, ws, na, it, mode);
+}
 template <typename T>
 static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
     if (cd.n_ns <= 0) return;
-    if (na.persistent)
-        hipLaunchKernelGGL(k_ns64_pq<T>, dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.n_ns,
-                           launch_queue(cd, it, mode, 0), ws, na, it, mode);
-    else
-        hipLaunchKernelGGL(k_ns64<T>, dim3(cd.n_ns), dim3(256), 0, st, cd, ws, na, it, mode);
+    if (cd.ns_wide) launch_64<T, 4>(cd, ws, na, it, mode, st);
+    else launch_64<T, 2>(cd, ws, na, it, mode, st);
 }
 
 hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it, hipStream_t st) {

@@ -520,6 +520,18 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                 ch.off_ictl = ch.off_q;
                 ch.off_q += align256(js.size() * sizeof(InvCtl));
             }
+            // FP64/FP32: tasks of two 64-column tiles run the matrix cores
+            // fuller, but only where they still give every CU its two
+            // workgroups twice over (256 CUs); a smaller chunk is bound by
+            // the time of one task
+            if (pl->prec == NOLSM_FP64 || pl->prec == NOLSM_FP32) {
+                size_t wide = 0;
+                for (int32_t g : js) {
+                    const size_t nt = (size_t)np_of(g) / NOLSM_TILE;
+                    wide += nt * ((nt + 1) / 2);
+                }
+                ch.ns_wide = wide >= 1024;
+            }
             size_t off = ch.off_q + qbytes;
             for (size_t s = 0; s < js.size(); ++s) {
                 const int32_t g = js[s];
@@ -580,8 +592,9 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                     (T == 64 && (pl->prec == NOLSM_FP16 || pl->prec == NOLSM_BF16)) ? ch.t_ns64 : ch.t_ns;
                 // symmetric route: upper tiles only, each mirrors itself
                 const bool sym = pl->sym != 0;
+                const int32_t bstep = ch.ns_wide ? 2 : 1;
                 for (int32_t a = 0; a < nt; ++a)
-                    for (int32_t b = sym ? a : 0; b < nt; ++b) tl.push_back(NOLSM_TASK(s, a, b));
+                    for (int32_t b = sym ? a : 0; b < nt; b += bstep) tl.push_back(NOLSM_TASK(s, a, b));
                 // (slot, 256-row block, owned molecule): the molecules of one row
                 // block are adjacent, so they run together on one XCD and share
                 // the streamed rows through its L2

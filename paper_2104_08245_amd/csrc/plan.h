@@ -14,6 +14,7 @@ struct HostChunk {
     std::vector<uint32_t> t_subst, t_conv, t_ns, t_ns64, t_rows;
     int32_t max_m = 0, max_np = 0, max_own = 1;
     size_t n_ns_real = 0, n_ns64_real = 0;   // task counts before padding
+    bool ns_wide = false;     // FP64/FP32: tasks of two 64-column tiles
     size_t ws_used = 0;       // bytes of the workspace this chunk uses
     size_t off_ctl = 0;       // workspace offset of the SubCtl array
     size_t off_ictl = 0;      // workspace offset of the InvCtl array (0: none)
