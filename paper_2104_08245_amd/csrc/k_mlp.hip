@@ -22,10 +22,6 @@
 static_assert(NPAR == NOLSM_MLP_NPARAM, "parameter packing");
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
-__device__ __forceinline__ float dsilu(float z) {
-    const float s = 1.0f / (1.0f + expf(-z));
-    return s * (1.0f + z * (1.0f - s));
-}
 
 // one thread per sample; parameters staged in LDS
 __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ prm, const float *__restrict__ norm,
@@ -57,113 +53,219 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ p
     out[(int64_t)b * 2 + 1] = o1;
 }
 
-// Loss and gradient over a batch, one workgroup of 16 waves. Wave w takes
-// samples w, w+16, ...; lane j owns hidden unit j and keeps its share of the
-// gradient in registers (gW2[:, j], gW1[j, :], gW3[:, j], gb1[j], gb2[j]);
-// the 16 per-wave gradients are then summed in wave order (deterministic).
-#define NWAVE 16
-__global__ __launch_bounds__(1024) void k_mlp_loss_grad(const float *__restrict__ prm, const float *__restrict__ norm,
+// Loss and gradient over a batch on the FP32 matrix cores
+// (v_mfma_f32_16x16x4_f32). Each wave takes 16 samples at a time through the
+// whole network: A operands are samples by units, and a layer's result (lane
+// l, element e of block j: sample 4 (l / 16) + e, unit 16 j + l % 16) is
+// turned into the next A operand through the wave's own LDS rows, with no
+// barrier. As the operands of a product over the samples (the weights'
+// gradients) the results serve as they lie. Four workgroups share the work
+// by hidden unit: each runs the forward pass of every sample, workgroup g
+// forms the gradients that end in block g of 16 units (columns 16 g .. of
+// W2, rows 16 g .. of W1 and so on). Nothing is summed across workgroups, so
+// no scratch memory is needed; the waves' sums are added in wave order
+// (deterministic). One workgroup with a lane per unit, its weights and
+// activations read from LDS for every product, was bound by those reads: a
+// step (this and Adam) of 256 samples took 94 us, now 25; of 1,024, 280 and 76.
+// Eight waves of up to 256 registers: with sixteen of 128 it spilled (45 us).
+#define NWAVE 8
+#define LDW 68   // LDS row stride: rows 4 banks apart, 16 rows x 4 k distinct
+typedef float f4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4 mma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+// SiLU and its derivative from one exponential
+__device__ __forceinline__ void silu2(float z, float &h, float &d) {
+    const float s = 1.0f / (1.0f + expf(-z));
+    h = z * s;
+    d = s * (1.0f + z * (1.0f - s));
+}
+__device__ __forceinline__ float sum16(float v) {   // over the 16 lanes of a group
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+__device__ __forceinline__ float sum4(float v) {    // over the four groups
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
+__global__ __launch_bounds__(NWAVE * 64) void k_mlp_loss_grad(const float *__restrict__ prm, const float *__restrict__ norm,
                                                         const float *__restrict__ x, const float *__restrict__ y,
                                                         int B, float *__restrict__ grad, float *__restrict__ loss_out) {
-    __shared__ float P[NPAR];
-    __shared__ float W2T[NH * NH];
-    __shared__ float nm[2 * NF];
-    __shared__ float xs[NWAVE][NF];
-    __shared__ float h1s[NWAVE][NH];
-    __shared__ float gz2s[NWAVE][NH];
-    __shared__ float G[NPAR];
-    __shared__ float lw[NWAVE];
-    const int t = threadIdx.x, w = t >> 6, j = t & 63;
-    for (int i = t; i < NPAR; i += 1024) P[i] = prm[i];
-    for (int i = t; i < NH * NH; i += 1024) {
-        const int r = i / NH, c = i % NH;
-        W2T[c * NH + r] = prm[OFF_W2 + i];
+    __shared__ float W2[NH * LDW];
+    __shared__ float act[NWAVE][16 * LDW];   // a wave's 16 samples x 64 units; then its gradient sums
+    __shared__ float part[NWAVE][16 * 16 + 64];
+    const int t = threadIdx.x, w = t >> 6, l = t & 63, li = l & 15, lk = l >> 4, g = blockIdx.x;
+    for (int i = t; i < NH * NH; i += NWAVE * 64) W2[(i / NH) * LDW + i % NH] = prm[OFF_W2 + i];
+    // weights of this lane's units and of the first layer's B operand
+    // (W1[16 j + li][4 s + lk])
+    float w1[3][4], b1[4], b2[4], w30[4], w31[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int u = 16 * j + li;
+        b1[j] = prm[OFF_B1 + u];
+        b2[j] = prm[OFF_B2 + u];
+        w30[j] = prm[OFF_W3 + u];
+        w31[j] = prm[OFF_W3 + NH + u];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) w1[s][j] = prm[u * NF + 4 * s + lk];
     }
-    for (int i = t; i < 2 * NF; i += 1024) nm[i] = norm[i];
+    const float b30 = prm[OFF_B3], b31 = prm[OFF_B3 + 1];
+    const float xm = li < NF ? norm[li] : 0.0f, xd = li < NF ? norm[NF + li] : 1.0f;
+    float am[3], ad[3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        am[s] = norm[4 * s + lk];
+        ad[s] = norm[NF + 4 * s + lk];
+    }
     __syncthreads();
-    float gW2[NH], gW1[NF], gW3[NO], gb1 = 0, gb2 = 0, gb3[NO] = {0, 0}, lsum = 0;
-    for (int k = 0; k < NH; ++k) gW2[k] = 0;
-    for (int i = 0; i < NF; ++i) gW1[i] = 0;
-    gW3[0] = gW3[1] = 0;
+    f4 gW2[4], gW1 = {0, 0, 0, 0};   // blocks (k, g) of W2's gradient; rows 16 g .. of W1's, column 12 that of b1
+#pragma unroll
+    for (int i = 0; i < 4; ++i) gW2[i] = (f4){0, 0, 0, 0};
+    float gb2 = 0, gw30 = 0, gw31 = 0, gb30 = 0, gb31 = 0, lsum = 0;
     const float scale = 2.0f / (float)(B * NO);
-    const int rounds = (B + NWAVE - 1) / NWAVE;
-    for (int rd = 0; rd < rounds; ++rd) {
-        const int b = rd * NWAVE + w;
-        const bool valid = b < B;
-        if (valid && j < NF) xs[w][j] = (x[(int64_t)b * NF + j] - nm[j]) / nm[NF + j];
-        __syncthreads();
-        float z1 = 0, h1 = 0;
-        if (valid) {
-            z1 = P[OFF_B1 + j];
-            for (int i = 0; i < NF; ++i) z1 += P[j * NF + i] * xs[w][i];
-            h1 = silu(z1);
-            h1s[w][j] = h1;
+    float *const A = act[w];
+    for (int s0 = w * 16; s0 < B; s0 += 16 * NWAVE) {
+        // layer 1: sample li as the A operand's row
+        // W2's LDS rows through an offset that the compiler takes as new in
+        // every pass: it would keep all of them in registers, and spill
+        int o2 = 0;
+        asm volatile("" : "+v"(o2));
+        const float *const W = W2 + o2;
+        f4 z1[4], h1[4];
+        float dz1[4];   // d h1 / d z1 of block g
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z1[j] = (f4){b1[j], b1[j], b1[j], b1[j]};
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const float a = s0 + li < B ? (x[(int64_t)(s0 + li) * NF + 4 * s + lk] - am[s]) / ad[s] : 0.0f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z1[j] = mma4(a, w1[s][j], z1[j]);
         }
-        __syncthreads();
-        float z2 = 0, h2 = 0, go0 = 0, go1 = 0;
-        if (valid) {
-            z2 = P[OFF_B2 + j];
-            for (int i = 0; i < NH; ++i) z2 += W2T[i * NH + j] * h1s[w][i];
-            h2 = silu(z2);
-            float o0 = P[OFF_W3 + j] * h2, o1 = P[OFF_W3 + NH + j] * h2;
-            for (int off = 32; off > 0; off >>= 1) {
-                o0 += __shfl_xor(o0, off, 64);
-                o1 += __shfl_xor(o1, off, 64);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float h, d;
+                silu2(z1[j][e], h, d);
+                h1[j][e] = h;
+                if (j == g) dz1[e] = d;
+                A[(4 * lk + e) * LDW + 16 * j + li] = h;
             }
-            o0 += P[OFF_B3];
-            o1 += P[OFF_B3 + 1];
-            const float d0 = o0 - y[(int64_t)b * 2], d1 = o1 - y[(int64_t)b * 2 + 1];
-            const float w0 = d0 < 0 ? 4.0f : 1.0f, w1 = d1 < 0 ? 4.0f : 1.0f;
-            lsum += w0 * d0 * d0 + w1 * d1 * d1;
-            go0 = scale * w0 * d0;
-            go1 = scale * w1 * d1;
-            gW3[0] += go0 * h2;
-            gW3[1] += go1 * h2;
-            gb3[0] += go0;
-            gb3[1] += go1;
-            const float gh2 = go0 * P[OFF_W3 + j] + go1 * P[OFF_W3 + NH + j];
-            gz2s[w][j] = gh2 * dsilu(z2);
+        // layer 2 (the wave's own rows: its LDS accesses are in order)
+        f4 z2[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z2[j] = (f4){b2[j], b2[j], b2[j], b2[j]};
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            const float a = A[li * LDW + 4 * s + lk];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z2[j] = mma4(a, W[(16 * j + li) * LDW + 4 * s + lk], z2[j]);
         }
-        __syncthreads();
-        if (valid) {
-            float gh1 = 0;
-            for (int k = 0; k < NH; ++k) {
-                const float g = gz2s[w][k];
-                gh1 += g * P[OFF_W2 + k * NH + j];
-                gW2[k] += g * h1;
+        // outputs, loss and their gradients, one sample per element
+        f4 gz2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int b = s0 + 4 * lk + e;
+            const bool valid = b < B;
+            float h2[4], dz2[4], o0 = 0, o1 = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                silu2(z2[j][e], h2[j], dz2[j]);
+                o0 += w30[j] * h2[j];
+                o1 += w31[j] * h2[j];
             }
-            gb2 += gz2s[w][j];
-            const float gz1 = gh1 * dsilu(z1);
-            for (int i = 0; i < NF; ++i) gW1[i] += gz1 * xs[w][i];
-            gb1 += gz1;
+            o0 = sum16(o0) + b30;
+            o1 = sum16(o1) + b31;
+            const float d0 = valid ? o0 - y[(int64_t)b * 2] : 0.0f, d1 = valid ? o1 - y[(int64_t)b * 2 + 1] : 0.0f;
+            const float q0 = d0 < 0 ? 4.0f : 1.0f, q1 = d1 < 0 ? 4.0f : 1.0f;
+            const float go0 = scale * q0 * d0, go1 = scale * q1 * d1;
+            lsum += q0 * d0 * d0 + q1 * d1 * d1;
+            gb30 += go0;
+            gb31 += go1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                gz2[j][e] = (go0 * w30[j] + go1 * w31[j]) * dz2[j];
+                if (j == g) {
+                    gw30 += go0 * h2[j];
+                    gw31 += go1 * h2[j];
+                    gb2 += gz2[j][e];
+                }
+            }
         }
-        __syncthreads();
+        // W2's gradient, columns 16 g ..: sum over samples of gz2[k] h1[i]
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j == g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) gW2[i] = mma4(gz2[i][e], h1[j][e], gW2[i]);
+        // back through W2 to block g of layer 1
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) A[(4 * lk + e) * LDW + 16 * j + li] = gz2[j][e];
+        f4 gh1 = {0, 0, 0, 0}, gh1b = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 16; s += 2) {
+            gh1 = mma4(A[li * LDW + 4 * s + lk], W[(4 * s + lk) * LDW + 16 * g + li], gh1);
+            gh1b = mma4(A[li * LDW + 4 * s + 4 + lk], W[(4 * s + 4 + lk) * LDW + 16 * g + li], gh1b);
+        }
+        // W1's gradient, rows 16 g ..; column 12 of the samples is one (b1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int b = s0 + 4 * lk + e;
+            const float xs = li < NF ? (b < B ? (x[(int64_t)b * NF + li] - xm) / xd : 0.0f) : (li == NF ? 1.0f : 0.0f);
+            gW1 = mma4((gh1[e] + gh1b[e]) * dz1[e], xs, gW1);
+        }
     }
-    // deterministic reduction in wave order
-    for (int ww = 0; ww < NWAVE; ++ww) {
-        if (w == ww) {
-            const bool first = ww == 0;
-            for (int i = 0; i < NF; ++i) G[j * NF + i] = (first ? 0.0f : G[j * NF + i]) + gW1[i];
-            G[OFF_B1 + j] = (first ? 0.0f : G[OFF_B1 + j]) + gb1;
-            for (int k = 0; k < NH; ++k) G[OFF_W2 + k * NH + j] = (first ? 0.0f : G[OFF_W2 + k * NH + j]) + gW2[k];
-            G[OFF_B2 + j] = (first ? 0.0f : G[OFF_B2 + j]) + gb2;
-            G[OFF_W3 + j] = (first ? 0.0f : G[OFF_W3 + j]) + gW3[0];
-            G[OFF_W3 + NH + j] = (first ? 0.0f : G[OFF_W3 + NH + j]) + gW3[1];
-            if (j == 0) {
-                G[OFF_B3] = (first ? 0.0f : G[OFF_B3]) + gb3[0];
-                G[OFF_B3 + 1] = (first ? 0.0f : G[OFF_B3 + 1]) + gb3[1];
-            }
-        }
-        __syncthreads();
+    // the waves' sums side by side in LDS, then added in wave order
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) A[(16 * i + 4 * lk + e) * 16 + li] = gW2[i][e];
+    float *const P = part[w];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) P[(4 * lk + e) * 16 + li] = gW1[e];
+    gb2 = sum4(gb2);
+    gw30 = sum4(gw30);
+    gw31 = sum4(gw31);
+    gb30 = sum4(gb30);
+    gb31 = sum4(gb31);
+    lsum = sum4(lsum);
+    if (l < 16) {
+        P[256 + l] = gb2;
+        P[272 + l] = gw30;
+        P[288 + l] = gw31;
     }
-    // per-wave loss: lane sums are lane-uniform; lane 0 holds the wave total
-    if (j == 0) lw[w] = lsum;
+    if (l == 0) {
+        P[304] = gb30;
+        P[305] = gb31;
+        P[306] = lsum;
+    }
     __syncthreads();
-    for (int i = t; i < NPAR; i += 1024) grad[i] = G[i];
-    if (t == 0) {
-        float L = 0;
-        for (int ww = 0; ww < NWAVE; ++ww) L += lw[ww];
-        *loss_out = L / (float)(B * NO);
+    for (int i = t; i < NH * 16; i += NWAVE * 64) {
+        float v = 0.0f;
+        for (int q = 0; q < NWAVE; ++q) v += act[q][i];
+        grad[OFF_W2 + (i >> 4) * NH + 16 * g + (i & 15)] = v;
+    }
+    if (t < 307) {
+        float v = 0.0f;
+        for (int q = 0; q < NWAVE; ++q) v += part[q][t];
+        const int r = t >> 4, c = t & 15;
+        if (t < 256) {
+            if (c < NF) grad[(16 * g + r) * NF + c] = v;
+            else if (c == NF) grad[OFF_B1 + 16 * g + r] = v;
+        } else if (t < 272) {
+            grad[OFF_B2 + 16 * g + c] = v;
+        } else if (t < 288) {
+            grad[OFF_W3 + 16 * g + c] = v;
+        } else if (t < 304) {
+            grad[OFF_W3 + NH + 16 * g + c] = v;
+        } else if (g == 0) {
+            if (t < 306) grad[OFF_B3 + t - 304] = v;
+            else *loss_out = v / (float)(B * NO);
+        }
     }
 }
 
@@ -193,7 +295,7 @@ extern "C" int nolsm_mlp_forward(const float *d_params, const float *d_norm, con
 extern "C" int nolsm_mlp_loss_grad(const float *d_params, const float *d_norm, const float *d_x, const float *d_y,
                                    int32_t B, float *d_grad, float *d_loss, void *stream) {
     if (!d_params || !d_norm || !d_x || !d_y || !d_grad || !d_loss || B < 1) return NOLSM_E_ARG;
-    hipLaunchKernelGGL(k_mlp_loss_grad, dim3(1), dim3(1024), 0, (hipStream_t)stream, d_params, d_norm, d_x, d_y, B,
+    hipLaunchKernelGGL(k_mlp_loss_grad, dim3(NH / 16), dim3(NWAVE * 64), 0, (hipStream_t)stream, d_params, d_norm, d_x, d_y, B,
                        d_grad, d_loss);
     return hipGetLastError() == hipSuccess ? NOLSM_OK : NOLSM_E_HIP;
 }
