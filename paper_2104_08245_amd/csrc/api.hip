@@ -170,6 +170,7 @@ static LaunchArgs make_args(const nolsm_plan *pl, const BatchArgs &b) {
     ia.rmax = na.rmax;
     ia.own_pos = ga.own_pos;
     ia.bs = pl->bs;
+    ia.pgrid = pl->pgrid;
     FinishArgs &fa = A.fa;
     fa.prec = o.prec;
     fa.nfinal = (o.prec == NOLSM_FP16 || o.prec == NOLSM_BF16) ? o.n_final_fp32 : 0;

@@ -23,9 +23,12 @@ enum { IACT_STOP = 0, IACT_UPDATE = 1 };
 
 // c = 1 / max row sum of |S_J| over the padded np x np matrix (padding rows
 // are identity), Y_0 = c S_J and Z_0 = I in 16 bits; one workgroup per slot.
+// Bound by two reads of S_J and the writes of Y_0 and Z_0: sixteen waves a
+// workgroup and 16-byte accesses keep enough of them in flight (600 slots of
+// about 612 rows: 1105 us, 2250 with four waves and an element per access).
 template <typename T>
-__global__ __launch_bounds__(256) void k_inv_init(ChunkDev cd, char *ws) {
-    __shared__ double red[256];
+__global__ __launch_bounds__(1024) void k_inv_init(ChunkDev cd, char *ws) {
+    __shared__ double red[16];
     const int s = blockIdx.x;
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
@@ -33,42 +36,55 @@ __global__ __launch_bounds__(256) void k_inv_init(ChunkDev cd, char *ws) {
     const int np = M.np, ldx = M.ldx, t = threadIdx.x, w = t >> 6, l = t & 63;
     const double *S = (const double *)(ws + M.offL);
     double mx = 0.0;
-    for (int r = w; r < np; r += 4) {
+    for (int r = w; r < np; r += 16) {
         double rs = 0.0;
+#pragma unroll 4
         for (int c = l; c < np; c += 64) rs += fabs(S[(int64_t)r * np + c]);
         mx = fmax(mx, wave_sum(rs));
     }
-    mx = block_max(mx, red);
+    if (l == 0) red[w] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) mx = fmax(mx, red[q]);
     const double c = 1.0 / mx;
     uint16_t *Y0 = (uint16_t *)(ws + M.offY0);
     uint16_t *Z0 = (uint16_t *)(ws + M.offZ0);
-    for (int r = w; r < np; r += 4)
-        for (int q = l; q < np; q += 64) {
-            Y0[(int64_t)r * ldx + q] = Lp<T>::enc((float)(c * S[(int64_t)r * np + q]));
-            Z0[(int64_t)r * ldx + q] = Lp<T>::enc(r == q ? 1.0f : 0.0f);
+    const int n8 = np / 8;
+    for (int f = t; f < np * n8; f += 1024) {
+        const int r = f / n8, q = (f - r * n8) * 8;
+        const double2 *src = (const double2 *)(S + (int64_t)r * np + q);
+        uint32_t y[4], z[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double2 v = src[k];
+            y[k] = Lp<T>::enc((float)(c * v.x)) | ((uint32_t)Lp<T>::enc((float)(c * v.y)) << 16);
+            z[k] = Lp<T>::enc(r == q + 2 * k ? 1.0f : 0.0f) | ((uint32_t)Lp<T>::enc(r == q + 2 * k + 1 ? 1.0f : 0.0f) << 16);
         }
+        *(uint4 *)(Y0 + (int64_t)r * ldx + q) = make_uint4(y[0], y[1], y[2], y[3]);
+        *(uint4 *)(Z0 + (int64_t)r * ldx + q) = make_uint4(z[0], z[1], z[2], z[3]);
+    }
     if (t == 0) {
         ic->done = 0;
         ic->iters = 0;
         ic->scale = c;
     }
-    for (int i = t; i < NOLSM_MAX_ITER_CAP; i += 256) ic->rhist[i] = 0.0;
+    for (int i = t; i < NOLSM_MAX_ITER_CAP; i += 1024) ic->rhist[i] = 0.0;
 }
 
-// Decision at the update of iteration `it`, taken by thread 0 of every
+// Decision at the update of iteration `it`, taken by wave 0 of every
 // workgroup of the slot from the finished residual partials; the tile-0
 // workgroup records it.
 __device__ int inv_decide(const InvArgs &ia, const SubMeta &M, InvCtl *ic, SubCtl *ctl, const char *ws, int it,
                           int tile) {
     const double *res = (const double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
     double ssum = 0.0;
-    for (int i = 0; i < M.ntile_ns; ++i) ssum += res[i];
-    const double r = sqrt(ssum);
+    for (int i = threadIdx.x; i < M.ntile_ns; i += 64) ssum += res[i];
+    const double r = sqrt(wave_sum(ssum));
     const double rprev = it > 0 ? ic->rhist[it - 1] : INFINITY;
     const bool stop = it >= 1 && r < ia.rmax && r > ia.theta * rprev;
     const bool diverge = !isfinite(r) || (it >= 1 && r > 2.0 * rprev && r > 1.0);
     const bool last = it + 1 >= ia.max_iter;
-    if (tile == 0) {
+    if (tile == 0 && threadIdx.x == 0) {
         ic->rhist[it] = r;
         if (stop || diverge || last) {
             ic->done = 1;
@@ -89,8 +105,8 @@ __device__ int inv_decide(const InvArgs &ia, const SubMeta &M, InvCtl *ic, SubCt
 // the update (0: Y, 1: Z).
 template <typename T, int BM>
 __device__ __forceinline__ void inv_tile(const ChunkDev &cd, uint32_t task, char *ws, const InvArgs &ia, int it,
-                                         int mode, int which) {
-    __shared__ double red[256];
+                                         int mode, int which, bool nt_out) {
+    __shared__ double red[4];
     __shared__ int act_s;
     if (task == NOLSM_TASK_NONE) return;
     const int s = task_slot(task), ti = task_a(task), tj = task_b(task);
@@ -98,13 +114,13 @@ __device__ __forceinline__ void inv_tile(const ChunkDev &cd, uint32_t task, char
     SubCtl *ctl = cd.ctl + s;
     InvCtl *ic = cd.ictl + s;
     const int np = M.np, nt = (np + BM - 1) / BM, tile = ti * nt + tj, ldx = M.ldx;
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
         int act;
         if (ctl->status != NOLSM_MOL_OK) act = IACT_STOP;
         else if (mode == IM_R) act = ic->done ? IACT_STOP : IACT_UPDATE;
         else if (mode == IM_UPD) act = ic->done ? IACT_STOP : inv_decide(ia, M, ic, ctl, ws, it, tile);
         else act = IACT_UPDATE;   // after the loop: every OK slot
-        act_s = act;
+        if (threadIdx.x == 0) act_s = act;
     }
     __syncthreads();
     if (act_s == IACT_STOP) return;
@@ -126,155 +142,160 @@ __device__ __forceinline__ void inv_tile(const ChunkDev &cd, uint32_t task, char
         default: Ag = Sinv; Bg = K16; break;
     }
     constexpr int WT = BM / 2, NB = WT / 32;
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
-    const int row0 = ti * BM, col0 = tj * BM;
-    const int nrec = ldx * ldx * 2;
-    v16f acc[NB][NB];
-    lp_tile_product<T, BM>(Ag, Bg, ldx, np, row0, col0, acc);
-    // element e of block (i, j): row er0 + i 32 + (e / 4) 8 + e % 4, column ec0 + j 32
-    const int er0 = row0 + wm * WT + (l >> 5) * 4, ec0 = col0 + wn * WT + (l & 31);
-    const uint32_t eo = (uint32_t)((er0 * ldx + ec0) * 2);
-#define INV_EOFF(i, j, e) ((((i) * 32 + ((e) >> 2) * 8 + ((e) & 3)) * ldx + (j) * 32) * 2)
-#define INV_ROW(i, e) (er0 + (i) * 32 + ((e) >> 2) * 8 + ((e) & 3))
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w >> 1, wn = w & 1;
+    uint16_t *st = lp_lds<BM>();
+    const int rl = wm * WT + (l & 31), cl = wn * WT + (l >> 5) * 4, row0 = ti * BM, col0 = tj * BM;
+    const double mu = ((const WsHeader *)ws)->mu, sc = (mode == IM_SQ) ? ic->scale : 0.0;
+    double part = 0.0;
+    auto finish = [&](v16f(&acc)[NB][NB]) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int r = rl + i * 32, c = cl + j * 32 + q * 8, gr = row0 + r, gc = col0 + c;
+                    uint2 *p = (uint2 *)(st + tile_idx<BM>(r, c));
+                    uint16_t h[4];
+                    if (mode == IM_A) {
+                        // A_J = S^-1 K_J - mu I in FP64 (columns np.. of the
+                        // K buffer hold Y_J)
+                        double *Kb = (double *)(ws + M.offK) + (int64_t)gr * (np + 64) + gc;
+                        double a[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) a[e] = (double)acc[i][j][4 * q + e] - (gr == gc + e ? mu : 0.0);
+                        *(double2 *)Kb = make_double2(a[0], a[1]);
+                        *(double2 *)(Kb + 2) = make_double2(a[2], a[3]);
+                        continue;
+                    }
+                    if (mode == IM_R) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = (gr == gc + e ? 1.0f : 0.0f) - acc[i][j][4 * q + e];
+                            part += (double)v * (double)v;
+                            h[e] = Lp<T>::enc(v);
+                        }
+                    } else if (mode == IM_UPD) {
+                        // Y_{k+1} = Y_k + Y_k R_k / 2 or Z_{k+1} = Z_k + R_k Z_k / 2
+                        const uint2 x = *p;
+                        const uint16_t y[4] = {(uint16_t)x.x, (uint16_t)(x.x >> 16), (uint16_t)x.y, (uint16_t)(x.y >> 16)};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) h[e] = enc_update<T>(y[e], acc[i][j][4 * q + e]);
+                    } else {
+                        // S^-1 = c Z_K^2 in 16 bits for the A GEMM; the columns
+                        // of every owned molecule o (block position q_o) also
+                        // go, from the FP32 accumulators, to its FP64 Y columns
+                        // np + o bs .. of the K buffer
+                        const int bs = ia.bs;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            h[e] = enc_scaled<T>((float)sc, acc[i][j][4 * q + e]);
+                            const int qb = (gc + e) / bs;
+                            for (int o = 0; o < M.nown; ++o)
+                                if (ia.own_pos[M.own_off + o] == qb)
+                                    ((double *)(ws + M.offK))[(int64_t)gr * (np + 64) + np + o * bs + (gc + e - qb * bs)] =
+                                        sc * (double)acc[i][j][4 * q + e];
+                        }
+                    }
+                    *p = pack4(h);
+                }
+    };
+    lp_tile_product<T, BM, false>(Ag, Bg, mode == IM_UPD ? (which ? Zc : Yc) : nullptr, ldx, np, ti, tj, true,
+                                  []() { return true; }, finish);
+    if (mode == IM_A) return;
     if (mode == IM_R) {
-        const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc((void *)Rb, (short)0, nrec, 0x00020000);
-        double part = 0.0;
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int gr = INV_ROW(i, e), gc = ec0 + j * 32;
-                    const float rr = (gr == gc ? 1.0f : 0.0f) - acc[i][j][e];
-                    __builtin_amdgcn_raw_buffer_store_b16(Lp<T>::enc(rr), rsR, eo, INV_EOFF(i, j, e), 0);
-                    if (gr < np && gc < np) part += (double)rr * (double)rr;
-                }
-        const double sum = block_sum(part, red);
-        if (threadIdx.x == 0) ((double *)(ws + M.offRes))[(int64_t)it * M.ntile_ns + tile] = sum;
-    } else if (mode == IM_UPD) {
-        // Y_{k+1} = Y_k + Y_k R_k / 2 or Z_{k+1} = Z_k + R_k Z_k / 2
-        const uint16_t *E = which ? Zc : Yc;
-        uint16_t *O = which ? Zn : Yn;
-        const __amdgpu_buffer_rsrc_t rsE = __builtin_amdgcn_make_buffer_rsrc((void *)E, (short)0, nrec, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rsO = __builtin_amdgcn_make_buffer_rsrc((void *)O, (short)0, nrec, 0x00020000);
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                uint16_t eo16[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) eo16[e] = __builtin_amdgcn_raw_buffer_load_b16(rsE, eo, INV_EOFF(i, j, e), 0);
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    __builtin_amdgcn_raw_buffer_store_b16(Lp<T>::enc(Lp<T>::dec(eo16[e]) + 0.5f * acc[i][j][e]), rsO,
-                                                          eo, INV_EOFF(i, j, e), 0);
-            }
-    } else if (mode == IM_SQ) {
-        // S^-1 = c Z_K^2 in 16 bits for the A GEMM; the columns of every
-        // owned molecule o (block position q_o) also go, from the FP32
-        // accumulators, to its FP64 Y columns np + o bs .. of the K buffer
-        const double c = ic->scale;
-        const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc((void *)Sinv, (short)0, nrec, 0x00020000);
-        double *Kb = (double *)(ws + M.offK);
-        const int ldk = np + 64, bs = ia.bs;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            // the output column of this lane in block column j, and its owner
-            const int gc = ec0 + j * 32, qb = gc / bs;
-            int yc = -1;
-            for (int o = 0; o < M.nown; ++o)
-                if (ia.own_pos[M.own_off + o] == qb) yc = np + o * bs + (gc - qb * bs);
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float v = (float)c * acc[i][j][e];
-                    __builtin_amdgcn_raw_buffer_store_b16(Lp<T>::enc(v), rsS, eo, INV_EOFF(i, j, e), 0);
-                    const int gr = INV_ROW(i, e);
-                    if (gr < np && gc < np && yc >= 0) Kb[(int64_t)gr * ldk + yc] = c * (double)acc[i][j][e];
-                }
-        }
-    } else {
-        // A_J = S^-1 K_J - mu I, FP64, rows and columns < np only (columns
-        // np.. of the K buffer hold Y_J)
-        const double mu = ((const WsHeader *)ws)->mu;
-        double *Kb = (double *)(ws + M.offK);
-        const int ldk = np + 64;
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int gr = INV_ROW(i, e), gc = ec0 + j * 32;
-                    if (gr < np && gc < np) Kb[(int64_t)gr * ldk + gc] = (double)acc[i][j][e] - (gr == gc ? mu : 0.0);
-                }
+        part = wave_sum(part);
+        if (l == 0) red[w] = part;
     }
-#undef INV_EOFF
-#undef INV_ROW
+    __syncthreads();
+    if (mode == IM_R && threadIdx.x == 0)
+        ((double *)(ws + M.offRes))[(int64_t)it * M.ntile_ns + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+    tile_store<BM>(mode == IM_R ? Rb : mode == IM_SQ ? Sinv : which ? Zn : Yn, ldx, np, ti, tj, nt_out);
 }
 
 template <typename T, int BM>
 __global__ __launch_bounds__(256, 3) void k_inv_lp(ChunkDev cd, const uint32_t *tasks, char *ws, InvArgs ia, int it,
                                                 int mode) {
-    inv_tile<T, BM>(cd, xcd_task(tasks), ws, ia, it, mode, blockIdx.y);
+    inv_tile<T, BM>(cd, xcd_task(tasks), ws, ia, it, mode, blockIdx.y, lp_nt_out(gridDim.x, ia.pgrid));
 }
 
 // K_J (FP64, columns < np of the K buffer) to 16 bits in the Y1 buffer for
-// the A GEMM; one workgroup per slot.
+// the A GEMM; one workgroup per slot and 64 rows, eight values per thread.
 template <typename T>
 __global__ __launch_bounds__(256) void k_inv_k16(ChunkDev cd, char *ws) {
     const int s = blockIdx.x;
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
-    if (cd.ctl[s].status != NOLSM_MOL_OK) return;
-    const int np = M.np, ldx = M.ldx, w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if ((int)blockIdx.y >= M.P || cd.ctl[s].status != NOLSM_MOL_OK) return;
+    const int np = M.np, ldx = M.ldx, r0 = blockIdx.y * 64, n8 = np / 8;
     const double *Kb = (const double *)(ws + M.offK);
     uint16_t *K16 = (uint16_t *)(ws + M.offY1);
-    for (int r = w; r < np; r += 4)
-        for (int q = l; q < np; q += 64) K16[(int64_t)r * ldx + q] = Lp<T>::enc((float)Kb[(int64_t)r * (np + 64) + q]);
+#pragma unroll 2
+    for (int f = threadIdx.x; f < 64 * n8; f += 256) {
+        const int r = r0 + f / n8, q = (f % n8) * 8;
+        const double2 *src = (const double2 *)(Kb + (int64_t)r * (np + 64) + q);
+        uint32_t y[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double2 v = src[k];
+            y[k] = Lp<T>::enc((float)v.x) | ((uint32_t)Lp<T>::enc((float)v.y) << 16);
+        }
+        *(uint4 *)(K16 + (int64_t)r * ldx + q) = make_uint4(y[0], y[1], y[2], y[3]);
+    }
 }
 
 // The bounds inputs the substitution would have written, from the FP64 A_J:
 // for 64-column tile cc, partial |A| row sums (columns < n) per row, the
 // complete |A| column sums (rows < n) and the tile's Frobenius share. Tasks
-// (slot, cc) with cc <= P; cc = P (the Y tile) has nothing to add.
+// (slot, cc) with cc <= P; cc = P (the Y tile) has nothing to add. Bound by
+// the read of A_J: its 64 x 64 blocks pass through LDS (coalesced 16-byte
+// loads, the next block's behind this one's sums), where wave 0 sums rows and
+// wave 1 columns, in the order of the elements. With a row per thread read
+// straight from memory 600 slots of about 612 rows took 2900 us; this, k_inv_init
+// and k_inv_k16 together went from 6290 to 2050 us.
 __global__ __launch_bounds__(256) void k_inv_sums(ChunkDev cd, char *ws) {
-    __shared__ double red[256];
+    __shared__ double tile[64][LDP];
     const uint32_t task = xcd_task(cd.t_subst);
     if (task == NOLSM_TASK_NONE) return;
     const int s = task_slot(task), cc = task_a(task);
     const SubMeta M = cd.meta[s];
     if (cd.ctl[s].status != NOLSM_MOL_OK || cc >= M.P) return;
-    const int n = M.n, np = M.np, t = threadIdx.x;
+    const int n = M.n, np = M.np, P = M.P, t = threadIdx.x;
     const int64_t ldk = np + 64;
-    const double *A = (const double *)(ws + M.offK);
+    const double *A = (const double *)(ws + M.offK) + cc * 64;
     double *rowp = (double *)(ws + M.offRow);
     double *colp = (double *)(ws + M.offCol);
-    double fs = 0.0;
-    for (int r = t; r < np; r += 256) {
-        double rs = 0.0;
-        if (r < n)
-            for (int c = 0; c < 64; ++c) {
-                const int gc = cc * 64 + c;
-                if (gc < n) {
-                    const double v = A[(int64_t)r * ldk + gc];
+    const int nc = min(64, n - cc * 64);   // columns of this tile inside the matrix (may be none)
+    double fs = 0.0, cs = 0.0;
+    RegTile<double> pl;
+    g2r_tile(pl, A, ldk);
+    for (int b = 0; b < P; ++b) {
+        r2s_tile(tile, pl);
+        __syncthreads();
+        if (b + 1 < P) g2r_tile(pl, A + (int64_t)(b + 1) * 64 * ldk, ldk);
+        if (t < 64) {
+            double rs = 0.0;
+            if (b * 64 + t < n)
+#pragma unroll 8
+                for (int c = 0; c < nc; ++c) {
+                    const double v = tile[t][c];
                     rs += fabs(v);
                     fs += v * v;
                 }
-            }
-        rowp[(int64_t)cc * np + r] = rs;
+            rowp[(int64_t)cc * np + b * 64 + t] = rs;
+        } else if (t < 128) {
+            const int nr = min(64, n - b * 64);
+#pragma unroll 8
+            for (int r = 0; r < nr; ++r) cs += fabs(tile[r][t - 64]);
+        }
+        __syncthreads();
     }
     if (t < 64) {
-        const int gc = cc * 64 + t;
-        double cs = 0.0;
-        if (gc < n)
-            for (int r = 0; r < n; ++r) cs += fabs(A[(int64_t)r * ldk + gc]);
-        colp[gc] = cs;
+        fs = wave_sum(fs);
+        if (t == 0) colp[np + cc] = fs;
+    } else if (t < 128) {
+        colp[cc * 64 + t - 64] = t - 64 < nc ? cs : 0.0;
     }
-    const double fsum = block_sum(fs, red);
-    if (t == 0) colp[np + cc] = fsum;
 }
 
 template <typename T>
@@ -289,12 +310,12 @@ static void launch_inv_gemm(const ChunkDev &cd, char *ws, const InvArgs &ia, int
 
 template <typename T>
 static hipError_t run_inverse(const ChunkDev &cd, char *ws, const InvArgs &ia, hipStream_t st) {
-    hipLaunchKernelGGL(k_inv_init<T>, dim3(cd.nsub), dim3(256), 0, st, cd, ws);
+    hipLaunchKernelGGL(k_inv_init<T>, dim3(cd.nsub), dim3(1024), 0, st, cd, ws);
     for (int it = 0; it < ia.max_iter; ++it) {
         launch_inv_gemm<T>(cd, ws, ia, it, IM_R, 1, st);
         launch_inv_gemm<T>(cd, ws, ia, it, IM_UPD, 2, st);
     }
-    hipLaunchKernelGGL(k_inv_k16<T>, dim3(cd.nsub), dim3(256), 0, st, cd, ws);
+    hipLaunchKernelGGL(k_inv_k16<T>, dim3(cd.nsub, cd.max_np / 64), dim3(256), 0, st, cd, ws);
     launch_inv_gemm<T>(cd, ws, ia, 0, IM_SQ, 1, st);
     launch_inv_gemm<T>(cd, ws, ia, 0, IM_A, 1, st);
     hipLaunchKernelGGL(k_inv_sums, dim3(cd.n_subst), dim3(256), 0, st, cd, ws);

@@ -356,15 +356,6 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64_pq(ChunkDe
 }
 
 // ------------------------------------------------------------ FP16 / BF16
-// 16 bytes, past the caches (nt) where an output is read again only a whole
-// pass over a large chunk later: kept out of L2 it does not displace the
-// operand tiles that the workgroups beside it share
-__device__ __forceinline__ void store16(uint16_t *p, const uint4 &v, bool nt) {
-    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    const v4u x = {v.x, v.y, v.z, v.w};
-    if (nt) __builtin_nontemporal_store(x, (v4u *)p);
-    else *(v4u *)p = x;
-}
 // Output tile (ti, tj) of the symmetric iteration from its LDS copy
 // (tile_idx), 16-byte row stores of the rows and columns below np. A
 // diagonal tile is written exactly symmetric, from its upper triangle: X R
@@ -396,13 +387,15 @@ template <int BM> __device__ __forceinline__ void sym_store(uint16_t *X, int ldx
     }
 }
 
-// One upper BM x BM tile of the symmetric sign iteration (modes as below).
-// With 128-row tiles X_k and R are stored by their upper tiles, and so are
-// the results. What is left below the diagonal tiles is never read until it
-// is filled in for the returned iterate.
-template <typename T, int BM>
-__device__ __forceinline__ void ns_sym_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
-                                            int mode) {
+// One BM x BM tile of a sign-iteration GEMM: mode 1 forms R = I - X_k^2 and
+// the tile's share of ||R||_F^2, mode 2 decides stop / continue / restart and
+// forms X_{k+1} = X_k + X_k R / 2. SYM: the upper tiles of the symmetric
+// iteration; with 128-row tiles X_k and R are stored by their upper tiles,
+// and so are the results, and what is left below the diagonal tiles is never
+// read until it is filled in for the returned iterate.
+template <typename T, int BM, bool SYM>
+__device__ __forceinline__ void ns_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
+                                        int mode) {
     __shared__ double red[4];
     __shared__ int act_s;
     if (task == NOLSM_TASK_NONE) return;
@@ -428,8 +421,8 @@ __device__ __forceinline__ void ns_sym_tile(const ChunkDev &cd, uint32_t task, c
         __syncthreads();
         if (act_s == ACT_RESTART) {
             auto enc = [](double v) { return Lp<T>::enc((float)v); };
-            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, enc, true);
-            if (BM == 64 && ti != tj) restart_tile(M, ctl, ws, Xn, tj * BM, ti * BM, BM, BM, enc, true);
+            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, enc, SYM);
+            if (SYM && BM == 64 && ti != tj) restart_tile(M, ctl, ws, Xn, tj * BM, ti * BM, BM, BM, enc, true);
         }
         return act_s == ACT_UPDATE;
     };
@@ -447,15 +440,16 @@ __device__ __forceinline__ void ns_sym_tile(const ChunkDev &cd, uint32_t task, c
                 for (int q = 0; q < 4; ++q) {
                     const int r = rl + i * 32, c = cl + j * 32 + q * 8;
                     uint2 *p = (uint2 *)(st + tile_idx<BM>(r, c));
-                    float v[4];
+                    uint16_t o[4];
                     if (mode == 1) {
                         // R = I - X^2 is small near convergence and keeps full
                         // relative precision in 16 bits (3I - X^2 would not: its
                         // diagonal ~2 is quantised at 2^-9 in FP16)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            v[e] = ((ti == tj && r == c + e) ? 1.0f : 0.0f) - acc[i][j][4 * q + e];
-                            part += (double)v[e] * (double)v[e];
+                            const float v = ((ti == tj && r == c + e) ? 1.0f : 0.0f) - acc[i][j][4 * q + e];
+                            part += (double)v * (double)v;
+                            o[e] = Lp<T>::enc(v);
                         }
                     } else {
                         // X_{k+1} = X_k + X_k R / 2 = X_k (3I - X_k^2) / 2, X_k
@@ -463,27 +457,36 @@ __device__ __forceinline__ void ns_sym_tile(const ChunkDev &cd, uint32_t task, c
                         const uint2 x = *p;
                         const uint16_t h[4] = {(uint16_t)x.x, (uint16_t)(x.x >> 16), (uint16_t)x.y, (uint16_t)(x.y >> 16)};
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = Lp<T>::dec(h[e]) + 0.5f * acc[i][j][4 * q + e];
+                        for (int e = 0; e < 4; ++e) {
+                            if constexpr (SYM) {
+                                // rounded to FP32 and then to 16 bits
+                                float v = Lp<T>::dec(h[e]) + 0.5f * acc[i][j][4 * q + e];
+                                asm volatile("" : "+v"(v));
+                                o[e] = Lp<T>::enc(v);
+                            } else {
+                                o[e] = enc_update<T>(h[e], acc[i][j][4 * q + e]);
+                            }
+                        }
                     }
-                    *p = make_uint2((uint32_t)Lp<T>::enc(v[0]) | ((uint32_t)Lp<T>::enc(v[1]) << 16),
-                                    (uint32_t)Lp<T>::enc(v[2]) | ((uint32_t)Lp<T>::enc(v[3]) << 16));
+                    *p = pack4(o);
                 }
     };
-    if (!lp_sym_product<T, BM>(Xc, mode == 1 ? Xc : Bb, mode == 1 ? nullptr : Xc, ldx, np, ti, tj, !done, begin,
-                               finish))
+    if (!lp_tile_product<T, BM, SYM>(Xc, mode == 1 ? Xc : Bb, mode == 1 ? nullptr : Xc, ldx, np, ti, tj, !done,
+                                     begin, finish))
         return;
     if (mode == 1) {
-        // a value off the diagonal counts for its mirror too
-        part = wave_sum(part) * ((ti != tj || wm < wn) ? 2.0 : 1.0);
+        // SYM: a value off the diagonal counts for its mirror too
+        part = wave_sum(part) * ((SYM && (ti != tj || wm < wn)) ? 2.0 : 1.0);
         if (l == 0) red[w] = part;
     }
     __syncthreads();
     if (mode == 1 && threadIdx.x == 0) {
         double *res = (double *)(ws + M.offRes) + (int64_t)it * M.ntile_ns;
         res[tile] = (red[0] + red[1]) + (red[2] + red[3]);
-        if (ti != tj) res[tj * nt + ti] = 0.0;   // the mirror tile is never launched
+        if (SYM && ti != tj) res[tj * nt + ti] = 0.0;   // the mirror tile is never launched
     }
-    sym_store<BM>(mode == 1 ? Bb : Xn, ldx, np, ti, tj, na.nt_out);
+    if constexpr (SYM) sym_store<BM>(mode == 1 ? Bb : Xn, ldx, np, ti, tj, na.nt_out);
+    else tile_store<BM>(mode == 1 ? Bb : Xn, ldx, np, ti, tj, na.nt_out);
 }
 
 // Fills in the tiles below the diagonal of the returned iterate, which the
@@ -501,99 +504,6 @@ __global__ __launch_bounds__(256) void k_ns_mirror(ChunkDev cd, char *ws) {
     const int w = threadIdx.x >> 6, r0 = ti * 128 + (w >> 1) * 64, c0 = tj * 128 + (w & 1) * 64;
     if (c0 >= M.np) return;   // ti < tj: r0 is below np
     mirror_block((uint16_t *)(ws + ((ctl->iters & 1) ? M.offX1 : M.offX0)), M.ldx, r0, c0);
-}
-
-// One BM x BM tile of a sign-iteration GEMM: mode 1 forms R = I - X_k^2 and
-// the tile's share of ||R||_F^2, mode 2 decides stop / continue / restart and
-// forms X_{k+1} = X_k + X_k R / 2.
-template <typename T, int BM>
-__device__ __forceinline__ void ns_lp_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
-                                           int mode) {
-    __shared__ double red[256];
-    __shared__ int act_s;
-    if (task == NOLSM_TASK_NONE) return;
-    const int s = task_slot(task), ti = task_a(task), tj = task_b(task);
-    const SubMeta M = cd.meta[s];
-    SubCtl *ctl = cd.ctl + s;
-    const int np = M.np, nt = (np + BM - 1) / BM, tile = ti * nt + tj;
-    uint16_t *Xc = (uint16_t *)(ws + ((it & 1) ? M.offX1 : M.offX0));
-    uint16_t *Xn = (uint16_t *)(ws + ((it & 1) ? M.offX0 : M.offX1));
-    uint16_t *Bb = (uint16_t *)(ws + M.offB);
-    // one thread reads the control state and decides for the whole workgroup
-    if (threadIdx.x < 64) {
-        const bool done = ctl->done != 0;
-        const int act = mode == 2 ? ns_decide(na, M, ctl, ws, it, tile, done) : (done ? ACT_STOP : ACT_UPDATE);
-        if (threadIdx.x == 0) act_s = act;
-    }
-    __syncthreads();
-    {
-        const int act = act_s;
-        if (act == ACT_STOP) return;
-        if (act == ACT_RESTART) {
-            restart_tile(M, ctl, ws, Xn, ti * BM, tj * BM, BM, BM, [](double v) { return Lp<T>::enc((float)v); });
-            return;
-        }
-    }
-    constexpr int WT = BM / 2, NB = WT / 32;
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
-    const int row0 = ti * BM, col0 = tj * BM, ldx = M.ldx;
-    const int nrec = ldx * ldx * 2;
-    v16f acc[NB][NB];
-    lp_tile_product<T, BM>(Xc, (mode == 1) ? Xc : Bb, ldx, np, row0, col0, acc);
-    // Epilogue over the whole tile, padding included: rows and columns in
-    // [np, ldx) of R and X_{k+1} only ever feed outputs that are never used,
-    // so the accesses need no bounds test and the X_k reads of the update
-    // are issued together rather than one guarded load at a time.
-    // element e of block (i, j) sits (i * 32 + (e / 4) * 8 + e % 4) rows and
-    // j * 32 columns from the lane's base: a uniform offset per element
-    const int er0 = row0 + wm * WT + (l >> 5) * 4, ec0 = col0 + wn * WT + (l & 31);
-    const uint32_t eo = (uint32_t)((er0 * ldx + ec0) * 2);
-#define NS_EOFF(i, j, e) ((((i) * 32 + ((e) >> 2) * 8 + ((e) & 3)) * ldx + (j) * 32) * 2)
-    if (mode == 1) {
-        const __amdgpu_buffer_rsrc_t rsR = __builtin_amdgcn_make_buffer_rsrc((void *)Bb, (short)0, nrec, 0x00020000);
-        double part = 0.0;
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int gr = er0 + i * 32 + (e >> 2) * 8 + (e & 3), gc = ec0 + j * 32;
-                    // R = I - X^2 is small near convergence and keeps full
-                    // relative precision in 16 bits (3I - X^2 would not: its
-                    // diagonal ~2 is quantised at 2^-9 in FP16)
-                    const float rr = (gr == gc ? 1.0f : 0.0f) - acc[i][j][e];
-                    __builtin_amdgcn_raw_buffer_store_b16(Lp<T>::enc(rr), rsR, eo, NS_EOFF(i, j, e), 0);
-                    if (gr < np && gc < np) part += (double)rr * (double)rr;
-                }
-        const double sum = block_sum(part, red);
-        if (threadIdx.x == 0) ((double *)(ws + M.offRes))[(int64_t)it * M.ntile_ns + tile] = sum;
-    } else {
-        const __amdgpu_buffer_rsrc_t rsX = __builtin_amdgcn_make_buffer_rsrc((void *)Xc, (short)0, nrec, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rsN = __builtin_amdgcn_make_buffer_rsrc((void *)Xn, (short)0, nrec, 0x00020000);
-        // X_{k+1} = X_k + X_k R / 2 = X_k (3I - X_k^2) / 2, one block at a time
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                uint16_t xo[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    xo[e] = __builtin_amdgcn_raw_buffer_load_b16(rsX, eo, NS_EOFF(i, j, e), 0);
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    __builtin_amdgcn_raw_buffer_store_b16(Lp<T>::enc(Lp<T>::dec(xo[e]) + 0.5f * acc[i][j][e]), rsN,
-                                                          eo, NS_EOFF(i, j, e), 0);
-            }
-    }
-#undef NS_EOFF
-}
-
-template <typename T, int BM, bool SYM>
-__device__ __forceinline__ void ns_tile(const ChunkDev &cd, uint32_t task, char *ws, const NsArgs &na, int it,
-                                        int mode) {
-    if constexpr (SYM) ns_sym_tile<T, BM>(cd, task, ws, na, it, mode);
-    else ns_lp_tile<T, BM>(cd, task, ws, na, it, mode);
 }
 
 template <typename T, int BM, bool SYM>
@@ -642,9 +552,7 @@ static int persistent_grid(const NsArgs &na, int ntask) {
 
 template <typename T, bool SYM>
 static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode, hipStream_t st) {
-    // more tiles than run at once (three workgroups per CU): their outputs
-    // leave the caches before the next launch reads them
-    na.nt_out = cd.n_ns > na.pgrid + na.pgrid / 2;
+    na.nt_out = lp_nt_out(cd.n_ns, na.pgrid);
     if (na.persistent) {
         if (cd.n_ns > 0)
             hipLaunchKernelGGL((k_ns_lp_pq<T, 128, SYM>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd,

@@ -41,7 +41,7 @@ struct NsArgs {
     int32_t persistent;    // queue-driven fixed grid instead of one workgroup per tile
     int32_t pgrid;         // workgroups of a persistent launch
     int32_t sym;           // symmetric sign iteration: upper tiles, mirrored (FP16/BF16)
-    int32_t nt_out;        // symmetric iteration: outputs stored past the caches (set per launch)
+    int32_t nt_out;        // 16-bit outputs stored past the caches (set per launch)
     int32_t force_stall;   // molecule taken as diverged at iteration NOLSM_STALL_IT (-1: none)
 };
 #define NOLSM_STALL_IT 2
@@ -54,6 +54,7 @@ struct InvArgs {
     double theta, rmax;
     const int32_t *own_pos;   // block position of each owned molecule (SubMeta::own_off)
     int32_t bs;
+    int32_t pgrid;         // twice the CUs
 };
 
 struct FinishArgs {

@@ -30,6 +30,24 @@ template <> struct Lp<__bf16> {
     static __device__ __forceinline__ float dec(uint16_t x) { return (float)__builtin_bit_cast(__bf16, x); }
 };
 
+// A product or sum rounded once to the 16-bit type (FP16: v_fma_mixlo_f16,
+// without a rounding to FP32 in between). The value is kept to itself, or
+// the compiler would round two of them to FP32 and convert the pair.
+__device__ __forceinline__ uint16_t alone(uint16_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+template <typename T> __device__ __forceinline__ uint16_t enc_update(uint16_t x, float acc) {   // x + acc / 2
+    return alone(Lp<T>::enc(Lp<T>::dec(x) + 0.5f * acc));
+}
+template <typename T> __device__ __forceinline__ uint16_t enc_scaled(float c, float acc) {
+    return alone(Lp<T>::enc(c * acc));
+}
+// four 16-bit values as two words
+__device__ __forceinline__ uint2 pack4(const uint16_t (&h)[4]) {
+    return make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+}
+
 #define LBK 64
 
 // LDS tiles hold 64 k per row (128 bytes, no padding). The 16-byte chunk c
@@ -47,194 +65,30 @@ template <int BM> __device__ __forceinline__ uint16_t *lp_lds() {
     return buf;
 }
 
-// acc = A[row0 .. row0 + BM, 0 .. np) * B[0 .. np, col0 .. col0 + BM): one
-// BM x BM tile (BM = 128: each of the 4 waves 64x64 as 2x2 32x32 MFMA blocks;
-// BM = 64: one 32x32 block per wave), K in slices of 64. A is staged in LDS
-// as [m][k]; B is read row-major from HBM and transposed on its way into LDS
-// ([n][k]) so that both MFMA operands are 16-byte LDS reads of 8 consecutive
-// k. On return, element e of block (i, j) of the calling lane holds output
-// row wm WT + i 32 + (e / 4) 8 + (l / 32) 4 + e % 4 and column
-// wn WT + j 32 + l % 32 of the tile (w = wave = 2 wm + wn, l = lane,
-// WT = BM / 2). All 256 threads must call it.
-// BSYM: B is symmetric, so B[k][n] = B[n][k] and its tile is loaded by rows
-// exactly like A (no transposition on the way into LDS).
-// SAME (with BSYM): B is A and col0 = row0 (a diagonal tile of X X with X
-// symmetric), so the B tile would equal the A tile: only A is loaded, and the
-// products read both operands from it.
-template <typename T, int BM, bool BSYM = false, bool SAME = false>
-__device__ __forceinline__ void lp_tile_product(const uint16_t *Ag, const uint16_t *Bg, int ldx, int np, int row0,
-                                                int col0, v16f (&acc)[BM / 64][BM / 64]) {
-    typedef typename Lp<T>::vec vec;
-    static_assert(!SAME || BSYM, "a shared operand tile needs B loaded by rows like A");
-    constexpr int WT = BM / 2;          // wave tile
-    constexpr int NB = WT / 32;         // 32x32 MFMA blocks per wave dimension
-    constexpr int AQ = BM / 32;         // 16-byte A loads per thread
-    constexpr int BT = 2 * BM;          // threads that load a 4(k) x 8(n) B block
-    uint16_t(*sA)[BM * LBK] = (uint16_t(*)[BM * LBK])lp_lds<BM>();
-    uint16_t(*sB)[BM * LBK] = (uint16_t(*)[BM * LBK])(lp_lds<BM>() + BM * LBK);
-    const int t = threadIdx.x, w = t >> 6, l = t & 63;
-    const int wm = w >> 1, wn = w & 1;
-    const int ac = (t & 7) * 8;
-    const bool bload = BSYM || (BT >= 256) || t < BT;   // BM = 128: every thread
-    // B block of thread t: k rows 4 kq .. 4 kq + 3, columns 8 nci .. 8 nci + 7.
-    // Each group of 16 lanes covers 8 column blocks and two k quads, so its
-    // 8-byte LDS stores land on 16 distinct 8-byte bank slots.
-    const int nci = (BM == 128) ? ((t & 7) | (((t >> 4) & 1) << 3)) : (t & 7);
-    const int kq = (BM == 128) ? (((t >> 3) & 1) | ((t >> 5) << 1)) : (t >> 3);
-    const int nc = nci * 8;
-    // The buffers have ldx >= the tile extent rows and columns, so loads need
-    // no masking: rows of A / columns of B past np only feed outputs that are
-    // never stored (an output (r, c) reads only row r of A and column c of B),
-    // and the k range stops at np. Staging is straight-line code on named
-    // registers (no arrays or lambdas, which the compiler spilled to scratch).
-    // Slices are fetched with raw buffer loads over the ldx x ldx buffers:
-    // a 32-bit lane offset plus a uniform row-block offset. A slice past the
-    // end (and B for threads that stage none) gets a lane offset beyond the
-    // buffer size, which the hardware answers with zeros and no memory
-    // access, so every load is unconditional and the compiler's wait counts
-    // stay exact across the prefetch ring.
-    const int nrec = ldx * ldx * 2;
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void *)Ag, (short)0, nrec, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc((void *)Bg, (short)0, nrec, 0x00020000);
-    const uint32_t va = (uint32_t)(((row0 + (t >> 3)) * ldx + ac) * 2);
-    const uint32_t vb = BSYM ? (uint32_t)(((col0 + (t >> 3)) * ldx + ac) * 2)
-                             : (uint32_t)((kq * 4 * ldx + col0 + nc) * 2);
-    const int sa32 = 64 * ldx, srow = 2 * ldx;   // bytes of 32 rows / one row
-    const int nk = np / LBK;
-    // One LDS buffer and one register set per workgroup (32 KB of LDS and
-    // about 140 VGPRs for BM = 128), so three workgroups share a CU: slice
-    // kt + 1 is fetched into registers while slice kt is multiplied from LDS,
-    // and latency is hidden across workgroups rather than by a deeper ring.
-    const uint4 z4 = {0, 0, 0, 0};
-    uint4 pa0 = z4, pa1 = z4, pa2 = z4, pa3 = z4, pb0 = z4, pb1 = z4, pb2 = z4, pb3 = z4;
-#define NS_BUF(rs, vo, so) __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0))
-#define NS_GLOAD(S, ks)                                                          \
-    do {                                                                         \
-        const bool in_ = (ks) < nk;                                              \
-        const uint32_t oa_ = in_ ? va + (uint32_t)((ks) * LBK * 2) : 0x80000000u; \
-        const uint32_t ob_ = !(in_ && bload) ? 0x80000000u                      \
-                             : BSYM ? vb + (uint32_t)((ks) * LBK * 2)            \
-                                    : vb + (uint32_t)((ks) * LBK * srow);        \
-        S##a0 = NS_BUF(rsA, oa_, 0);                                             \
-        S##a1 = NS_BUF(rsA, oa_, sa32);                                          \
-        if constexpr (AQ > 2) {                                                  \
-            S##a2 = NS_BUF(rsA, oa_, 2 * sa32);                                  \
-            S##a3 = NS_BUF(rsA, oa_, 3 * sa32);                                  \
-        }                                                                        \
-        if constexpr (SAME) {                                                    \
-        } else if constexpr (BSYM) {                                             \
-            S##b0 = NS_BUF(rsB, ob_, 0);                                         \
-            S##b1 = NS_BUF(rsB, ob_, sa32);                                      \
-            if constexpr (AQ > 2) {                                              \
-                S##b2 = NS_BUF(rsB, ob_, 2 * sa32);                              \
-                S##b3 = NS_BUF(rsB, ob_, 3 * sa32);                              \
-            }                                                                    \
-        } else {                                                                 \
-            S##b0 = NS_BUF(rsB, ob_, 0);                                         \
-            S##b1 = NS_BUF(rsB, ob_, srow);                                      \
-            S##b2 = NS_BUF(rsB, ob_, 2 * srow);                                  \
-            S##b3 = NS_BUF(rsB, ob_, 3 * srow);                                  \
-        }                                                                        \
-    } while (0)
-// B is a 4(k) x 8(n) block in S##b0..S##b3 (one k row each); column j of it
-// becomes 4 consecutive k for LDS row n = nc + j
-#define NS_BCOL(S, j, W)                                                         \
-    do {                                                                         \
-        uint32_t lo_, hi_;                                                       \
-        if (((j) & 1) == 0) {                                                    \
-            lo_ = (S##b0.W & 0xFFFFu) | (S##b1.W << 16);                         \
-            hi_ = (S##b2.W & 0xFFFFu) | (S##b3.W << 16);                         \
-        } else {                                                                 \
-            lo_ = (S##b0.W >> 16) | (S##b1.W & 0xFFFF0000u);                     \
-            hi_ = (S##b2.W >> 16) | (S##b3.W & 0xFFFF0000u);                     \
-        }                                                                        \
-        *(uint2 *)&sB[buf_][lds_swz(nc + (j), kq >> 1) + (kq & 1) * 4] =         \
-            make_uint2(lo_, hi_);                                                \
-    } while (0)
-#define NS_SSTORE(S, bufi)                                                       \
-    do {                                                                         \
-        const int buf_ = (bufi);                                                 \
-        *(uint4 *)&sA[buf_][lds_swz(t >> 3, t & 7)] = S##a0;                     \
-        *(uint4 *)&sA[buf_][lds_swz((t >> 3) + 32, t & 7)] = S##a1;              \
-        if constexpr (AQ > 2) {                                                  \
-            *(uint4 *)&sA[buf_][lds_swz((t >> 3) + 64, t & 7)] = S##a2;          \
-            *(uint4 *)&sA[buf_][lds_swz((t >> 3) + 96, t & 7)] = S##a3;          \
-        }                                                                        \
-        if constexpr (SAME) {                                                    \
-        } else if constexpr (BSYM) {                                             \
-            *(uint4 *)&sB[buf_][lds_swz(t >> 3, t & 7)] = S##b0;                 \
-            *(uint4 *)&sB[buf_][lds_swz((t >> 3) + 32, t & 7)] = S##b1;          \
-            if constexpr (AQ > 2) {                                              \
-                *(uint4 *)&sB[buf_][lds_swz((t >> 3) + 64, t & 7)] = S##b2;      \
-                *(uint4 *)&sB[buf_][lds_swz((t >> 3) + 96, t & 7)] = S##b3;      \
-            }                                                                    \
-        } else if (bload) {                                                      \
-            NS_BCOL(S, 0, x); NS_BCOL(S, 1, x); NS_BCOL(S, 2, y);                \
-            NS_BCOL(S, 3, y); NS_BCOL(S, 4, z); NS_BCOL(S, 5, z);                \
-            NS_BCOL(S, 6, w); NS_BCOL(S, 7, w);                                  \
-        }                                                                        \
-    } while (0)
-// one k slice of MFMA work from LDS buffer bufi
-#define NS_COMPUTE(bufi)                                                         \
-    do {                                                                         \
-        _Pragma("unroll") for (int kk = 0; kk < LBK; kk += 16) {                 \
-            vec a[NB], b[NB];                                                    \
-            _Pragma("unroll") for (int i = 0; i < NB; ++i) a[i] =                \
-                *(const vec *)&sA[bufi][lds_swz(wm * WT + i * 32 + (l & 31),     \
-                                                (kk >> 3) + (l >> 5))];          \
-            _Pragma("unroll") for (int j = 0; j < NB; ++j) b[j] =                \
-                *(const vec *)&(SAME ? sA : sB)[bufi][lds_swz(wn * WT + j * 32 + (l & 31), \
-                                                (kk >> 3) + (l >> 5))];          \
-            _Pragma("unroll") for (int i = 0; i < NB; ++i)                       \
-                _Pragma("unroll") for (int j = 0; j < NB; ++j)                   \
-                    acc[i][j] = Lp<T>::mma(a[i], b[j], acc[i][j]);               \
-        }                                                                        \
-    } while (0)
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    NS_GLOAD(p, 0);
-    NS_SSTORE(p, 0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        NS_GLOAD(p, kt + 1);   // past the last slice: zeros, no memory access
-        // the loads stay ahead of the products: without this fence (and with
-        // a conditional store) the compiler sinks them behind the MFMAs,
-        // next to their use, and every slice waits out the full load latency
-        __builtin_amdgcn_sched_barrier(0);
-        NS_COMPUTE(0);
-        __syncthreads();
-        NS_SSTORE(p, 0);       // the last one stores zeros nothing reads
-        __syncthreads();
-    }
-#undef NS_BUF
-#undef NS_GLOAD
-#undef NS_BCOL
-#undef NS_SSTORE
-#undef NS_COMPUTE
-}
-
 // ---------------------------------------------------------------------------
-// Tile (ti, tj), ti <= tj, of A B for symmetric A and B that commute. With
-// 128-row tiles the operands are stored by their upper tiles (the diagonal
-// tiles whole): row block ti of A at the k's of tile row kb is the stored
-// tile (ti, kb) as it stands where kb >= ti, and the transpose of the stored
-// tile (kb, ti) where kb < ti; row block tj of B (B[k][n] = B[n][k])
-// likewise. A tile that is read transposed comes as 4 (k) x 8 blocks per
-// thread and is turned on its way into LDS, so both operands sit there as
-// [row][k]. Storing one triangle takes 0.6 of the memory traffic at 5 x 5
+// BM x BM tile (ti, tj) of A B (BM = 128: each of the 4 waves 64x64 as 2x2
+// 32x32 MFMA blocks; BM = 64: one 32x32 block per wave), K in slices of 64.
+// Both operands sit in LDS as [row of A or column of B][k], so that an MFMA
+// operand is one 16-byte read of 8 consecutive k.
+//
+// General matrices: A's rows come as they stand, B's k rows are read
+// transposed: 4 (k) x 8 blocks per thread, turned on their way into LDS.
+// SYM: A and B are symmetric and commute, and only tiles ti <= tj are formed.
+// With 128-row tiles the operands are stored by their upper tiles (the
+// diagonal tiles whole): row block ti of A at the k's of tile row kb is the
+// stored tile (ti, kb) as it stands where kb >= ti, and the transpose of the
+// stored tile (kb, ti) where kb < ti; row block tj of B (B[k][n] = B[n][k])
+// likewise. Storing one triangle takes 0.6 of the memory traffic at 5 x 5
 // tiles. 64-row tiles serve submatrices of one to three of them, which stay
 // in the caches: there both triangles are stored and nothing is turned.
 //
 // acc[i][j] holds the transposed MFMA block (operands swapped, the same
 // products in the same order): element e of the calling lane is tile row
 // wm WT + i 32 + l % 32 and column wn WT + j 32 + (e / 4) 8 + (l / 32) 4 +
-// e % 4, so four elements in turn are consecutive columns of one row.
-// Waves whose part of the tile is padding, or lies below the diagonal of a
-// diagonal tile, load and store with the others but do not multiply.
+// e % 4 (w = wave = 2 wm + wn, l = lane, WT = BM / 2), so four elements in
+// turn are consecutive columns of one row. Waves whose part of the tile is
+// padding, or lies below the diagonal of a diagonal tile (SYM), load and
+// store with the others but do not multiply.
 // ---------------------------------------------------------------------------
 // an output tile in LDS (the operand buffers, free after the product): rows
 // of BM values, 16-byte chunks swizzled by row
@@ -242,10 +96,35 @@ template <int BM> __device__ __forceinline__ int tile_idx(int r, int c) {
     return r * BM + (((c >> 3) ^ (r & (BM / 8 - 1))) << 3) + (c & 7);
 }
 
-template <int BM> __device__ __forceinline__ bool lp_sym_live(int np, int ti, int tj) {
+// 16 bytes, past the caches (nt) where an output is read again only a whole
+// pass over a large chunk later: kept out of L2 it does not displace the
+// operand tiles that the workgroups beside it share
+__device__ __forceinline__ void store16(uint16_t *p, const uint4 &v, bool nt) {
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    const v4u x = {v.x, v.y, v.z, v.w};
+    if (nt) __builtin_nontemporal_store(x, (v4u *)p);
+    else *(v4u *)p = x;
+}
+// tile (ti, tj) from its LDS copy, the rows and columns below np
+template <int BM> __device__ __forceinline__ void tile_store(uint16_t *X, int ldx, int np, int ti, int tj, bool nt) {
+    constexpr int NCH = BM / 8;
+    const uint16_t *st = lp_lds<BM>();
+    const int row0 = ti * BM, col0 = tj * BM;
+#pragma unroll 4
+    for (int f = threadIdx.x; f < BM * NCH; f += 256) {
+        const int r = f / NCH, c0 = (f % NCH) * 8;
+        if (row0 + r >= np || col0 + c0 >= np) continue;
+        store16(X + (int64_t)(row0 + r) * ldx + col0 + c0, *(const uint4 *)(st + tile_idx<BM>(r, c0)), nt);
+    }
+}
+// every launch of more tiles than run at once (three workgroups per CU, pgrid
+// being two): its outputs leave the caches before the next launch reads them
+__host__ __device__ __forceinline__ bool lp_nt_out(int ntask, int pgrid) { return ntask > pgrid + pgrid / 2; }
+
+template <int BM, bool SYM> __device__ __forceinline__ bool lp_live(int np, int ti, int tj) {
     constexpr int WT = BM / 2;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = w >> 1, wn = w & 1;
-    return ti * BM + wm * WT < np && tj * BM + wn * WT < np && !(ti == tj && wm > wn);
+    return ti * BM + wm * WT < np && tj * BM + wn * WT < np && !(SYM && ti == tj && wm > wn);
 }
 
 // `begin` runs between the issue of the first slice's loads and their use
@@ -255,16 +134,16 @@ template <int BM> __device__ __forceinline__ bool lp_sym_live(int np, int ti, in
 // `finish` takes the accumulators of the waves that multiply (the others run
 // a loop of their own, without products: a branch inside one loop would have
 // the accumulators copied).
-template <typename T, int BM, typename Begin, typename Finish>
-__device__ __forceinline__ bool lp_sym_product(const uint16_t *Ag, const uint16_t *Bg, const uint16_t *Eg, int ldx,
+template <typename T, int BM, bool SYM, typename Begin, typename Finish>
+__device__ __forceinline__ bool lp_tile_product(const uint16_t *Ag, const uint16_t *Bg, const uint16_t *Eg, int ldx,
                                                int np, int ti, int tj, bool pre, Begin begin, Finish finish) {
     typedef typename Lp<T>::vec vec;
     constexpr int WT = BM / 2, NB = WT / 32;
-    constexpr bool UP = BM == 128;   // stored by upper tiles
+    constexpr bool UP = SYM && BM == 128;   // stored by upper tiles
     uint16_t *lds = lp_lds<BM>();
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, wm = w >> 1, wn = w & 1;
-    const bool same = Ag == Bg && ti == tj;   // one operand tile serves both sides
-    const bool live = lp_sym_live<BM>(np, ti, tj);
+    const bool same = SYM && Ag == Bg && ti == tj;   // one operand tile serves both sides
+    const bool live = lp_live<BM, SYM>(np, ti, tj);
     const uint32_t none = 0x80000000u;        // beyond any buffer: zeros, no memory access
     const int nrec = ldx * ldx * 2, srow = 2 * ldx, nk = np / LBK;
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc((void *)Ag, (short)0, nrec, 0x00020000);
@@ -276,20 +155,23 @@ __device__ __forceinline__ bool lp_sym_product(const uint16_t *Ag, const uint16_
     // transposed: k rows 4 kq + q, columns 8 nci .. + 7; each group of 16
     // lanes covers 8 column blocks and two k quads, so that its 8-byte LDS
     // stores land on 16 distinct 8-byte bank slots
-    const int nci = (t & 7) | (((t >> 4) & 1) << 3), kq = ((t >> 3) & 1) | ((t >> 5) << 1);
+    // (64-row tiles: half of the threads)
+    const int nci = BM == 128 ? (t & 7) | (((t >> 4) & 1) << 3) : t & 7;
+    const int kq = BM == 128 ? ((t >> 3) & 1) | ((t >> 5) << 1) : t >> 3;
     const int nc = nci * 8;
+    const bool tl = BM == 128 || t < 128;
     const uint32_t ta = row0 + nc < np ? (uint32_t)(kq * 4 * srow + (row0 + nc) * 2) : none;
-    const uint32_t tb = col0 + nc < np ? (uint32_t)(kq * 4 * srow + (col0 + nc) * 2) : none;
+    const uint32_t tb = tl && col0 + nc < np ? (uint32_t)(kq * 4 * srow + (col0 + nc) * 2) : none;
     // the second half of a row block may be all padding (np is a multiple of 64)
     const bool a_hi = row0 + 64 < np, b_hi = col0 + 64 < np;
-    constexpr int NQ = BM / 32;   // 16-byte loads of an operand slice per thread
-    uint4 pf[2 * NQ];             // A's, then B's
+    constexpr int NQ = BM / 32, NB4 = SYM ? NQ : 4;   // 16-byte loads of A's and of B's slice per thread
+    uint4 pf[NQ + NB4];                               // A's, then B's
     auto load = [](const __amdgpu_buffer_rsrc_t &rs, uint32_t vo, int so) {
         return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0));
     };
     auto fetch = [&](int ks) {
         const int kb = ks * LBK / BM;
-        const bool tra = UP && kb < ti, trb = UP && kb < tj;
+        const bool tra = UP && kb < ti, trb = !SYM || (UP && kb < tj);
         const int sa = tra ? srow : 32 * srow, sb = trb ? srow : 32 * srow;
         const uint32_t oa = tra ? (ta == none ? none : ta + (uint32_t)(ks * LBK * srow)) : da + (uint32_t)(ks * LBK * 2);
         const uint32_t ob = same ? none
@@ -298,13 +180,13 @@ __device__ __forceinline__ bool lp_sym_product(const uint16_t *Ag, const uint16_
         const uint32_t oa2 = (tra || a_hi) ? oa : none, ob2 = (trb || b_hi) ? ob : none;
         pf[0] = load(rsA, oa, 0);
         pf[1] = load(rsA, oa, sa);
-        if constexpr (UP) {
+        if constexpr (NQ > 2) {
             pf[2] = load(rsA, oa2, 2 * sa);
             pf[3] = load(rsA, oa2, 3 * sa);
         }
         pf[NQ + 0] = load(rsB, ob, 0);
         pf[NQ + 1] = load(rsB, ob, sb);
-        if constexpr (UP) {
+        if constexpr (NB4 > 2) {
             pf[NQ + 2] = load(rsB, ob2, 2 * sb);
             pf[NQ + 3] = load(rsB, ob2, 3 * sb);
         }
@@ -321,7 +203,8 @@ __device__ __forceinline__ bool lp_sym_product(const uint16_t *Ag, const uint16_
         if (!tr) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) *(uint4 *)(s + ((wd ^ ((q & 1) << 6)) + q * 32 * LBK * 2)) = p[q];
-        } else if constexpr (UP) {
+        } else if constexpr (UP || !SYM) {
+            if (!tl) return;
             uint32_t o = wt;
             asm volatile("" : "+v"(o));   // the eight offsets are formed here, not kept through the loop
             auto col = [&](int j, uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3) {
@@ -342,7 +225,7 @@ __device__ __forceinline__ bool lp_sym_product(const uint16_t *Ag, const uint16_
     auto stash = [&](int ks) {
         const int kb = ks * LBK / BM;
         put(lb, pf, UP && kb < ti);
-        if (!same) put(lb + BM * LBK * 2, pf + NQ, UP && kb < tj);
+        if (!same) put(lb + BM * LBK * 2, pf + NQ, !SYM || (UP && kb < tj));
     };
     // tile (ti, tj) of Eg: chunk f % (BM / 8) of row f / (BM / 8), f = t + 256 q
     const int er = t / (BM / 8), ec = t % (BM / 8);
