@@ -1041,26 +1041,41 @@ __global__ __launch_bounds__(256, OCC) void k_subst_hl(ChunkDev cd, char *ws) {
     }
 }
 
-// A~ = W L^-T, two row blocks (i, i + 1) per launch: every tile of the factor
-// that the launch reads serves both rows, so the factor's lower triangle is
-// read half as often as with one row block per launch. First the three
-// tiles (i, i), (i, i + 1), (i + 1, i + 1), in that order (row i + 1 needs
-// X_{i+1,i} = X_{i,i+1}^T); then passes of RC column tiles j >= i + 2 with
-// both rows' accumulators in registers.
-template <int RC, int OCC>
-__global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, int i) {
+// A~ = W L^-T by column pairs: launch c (1 .. ceil(P / 2)) forms the tiles of
+// columns 2c, 2c + 1 above the diagonal, one workgroup per submatrix and row
+// pair (i, i + 1) = (2p, 2p + 1), p < c. X_ij needs X_ik, k < j: for k < i the
+// stored tile (k, i), for k >= i the row's own earlier tiles, all of earlier
+// launches, so the row pairs of a launch are independent. The diagonal tiles
+// of row pair c - 1 need its column tiles of the launch before; they come
+// first in that row pair's workgroup (p = c - 1): (i, i), (i, i + 1),
+// (i + 1, i + 1), in that order (row i + 1 needs X_{i+1,i} = X_{i,i+1}^T).
+// The row pairs of a submatrix run side by side on one XCD, and its L2 serves
+// the two rows of the factor to all of them. By row pairs (one workgroup per
+// submatrix and launch) every launch read the factor's lower triangle again
+// and few workgroups were in flight: 8.1 -> 7.3 ms for 4,096 submatrices of
+// about 612 rows, 21.7 -> 14.7 ms for a slab of 2,048 (340 to 1,520 rows).
+template <int OCC>
+__global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, int c) {
     const double mu = ((const WsHeader *)ws)->mu;
     __shared__ __attribute__((aligned(16))) HLTile sXa;   // operands of row i
     __shared__ __attribute__((aligned(16))) HLTile sXb;   // operands of row i + 1
     __shared__ __attribute__((aligned(16))) HLTile sL;    // L_jk or Dinv_j: B[k][n] = sL(n, k)
     __shared__ float sF[64][LDP];
     __shared__ double red[256];
-    const int s = blockIdx.x;
+    // workgroup b runs on XCD b % 8: the c row pairs of a submatrix in turn
+    // there. An XCD hands workgroups to its engines and CUs in turn, so for an
+    // even c the order turns with the submatrix: with the one of the diagonal
+    // tiles (the longest) always first a few CUs got all of those (3700 us for
+    // 2590 at c = 4, 4,096 submatrices of about 612 rows; for an odd c first
+    // is best, 1650 us for 2010 at c = 9 on the slab).
+    const int wb = blockIdx.x >> 3, q = wb / c, s = q * 8 + (blockIdx.x & 7);
+    const int p = (c & 1) ? c - 1 - wb % c : (wb + q) % c;
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
     if (cd.ctl[s].status != NOLSM_MOL_OK) return;
-    const int P = M.P, np = M.np, n = M.n;
-    if (i >= P) return;
+    const int P = M.P, np = M.np, n = M.n, i = 2 * p, j0 = 2 * c;
+    const bool diagonal = p == c - 1;
+    if (i >= P || (j0 >= P && !diagonal)) return;
     const bool two = i + 1 < P;
     const int64_t ldl = np, ldk = np + 64;
     const float *L = (const float *)(ws + (M.offL32 ? M.offL32 : M.offL));
@@ -1122,7 +1137,7 @@ __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, 
         mma64_hl(o, sXa, sL);
         __syncthreads();
     };
-    {
+    if (diagonal) {
         AccT<float> a00, a01, a11, o;
         g2acc(a00, Xt(i, i), ldk);
         acc_mul(a00, sc);
@@ -1166,8 +1181,9 @@ __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, 
             emit(o, i + 1, i + 1, frob1);
         }
     }
-    if (two) {
-        for (int j0 = i + 2; j0 < P; j0 += RC) {
+    if (j0 < P) {   // then row i + 1 is there too
+        {
+            constexpr int RC = 2;
             const int nr = min(RC, P - j0);
             AccT<float> a0[RC], a1[RC];
 #pragma unroll
@@ -1237,17 +1253,18 @@ __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, 
             }
         }
     }
-    // the row blocks are final: take mu off their diagonals
+    // no column pair left: the row blocks are final, take mu off their diagonals
     __syncthreads();
-    if (t < 64) {
+    if (j0 + 2 >= P && t < 64) {
         Kb[(int64_t)(i * 64 + t) * ldk + i * 64 + t] -= mu;
         if (two) Kb[(int64_t)((i + 1) * 64 + t) * ldk + (i + 1) * 64 + t] -= mu;
     }
     const double f0 = block_sum(frob0, red);
     const double f1 = block_sum(frob1, red);
     if (t == 0) {
-        ((double *)(ws + M.offCol))[np + i] = f0;
-        if (two) ((double *)(ws + M.offCol))[np + i + 1] = f1;
+        double *fp = (double *)(ws + M.offCol) + np + i;
+        fp[0] = diagonal ? f0 : fp[0] + f0;
+        if (two) fp[1] = diagonal ? f1 : fp[1] + f1;
     }
 }
 
@@ -1508,10 +1525,7 @@ hipError_t launch_subst_sym(const ChunkDev &cd, char *ws, bool fp32, bool split1
     const bool hl = fp32 && split16;
     // split products: two row tiles per pass fit three workgroups per CU
     // without spills (faster than four at two per CU). The right solve takes
-    // two row blocks per launch at two workgroups per CU (it spills a little
-    // there; at one per CU without spills the phase took 32% longer); with
-    // one row block per launch it read the factor twice as often and the
-    // phase took 9% longer.
+    // two row blocks and two column tiles per workgroup, two workgroups per CU.
     if (hl) {
         hipLaunchKernelGGL((k_subst_hl<2, 3>), dim3(cd.n_subst), dim3(256), 0, st, cd, ws);
     } else if (fp32) {
@@ -1523,8 +1537,8 @@ hipError_t launch_subst_sym(const ChunkDev &cd, char *ws, bool fp32, bool split1
     // row blocks in order: block i reads the finished blocks k < i
     const int pmax = cd.max_np / 64;
     if (hl) {
-        for (int i = 0; i < pmax; i += 2) {
-            hipLaunchKernelGGL((k_rsolve2_hl<2, 2>), dim3(cd.nsub), dim3(256), 0, st, cd, ws, i);
+        for (int c = 1; c <= (pmax + 1) / 2; ++c) {
+            hipLaunchKernelGGL(k_rsolve2_hl<2>, dim3((cd.nsub + 7) / 8 * 8 * c), dim3(256), 0, st, cd, ws, c);
             LAUNCH_CHECK();
         }
         return hipSuccess;
