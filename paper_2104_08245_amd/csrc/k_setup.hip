@@ -23,7 +23,10 @@
 // One workgroup per (block row a, submatrix). Each stored block (I, C) of
 // row I = N(J)_a is located in N(J) by one binary search, giving the inverse
 // map pos[b] = CSR entry of block column N(J)_b (or -1); the 6 x np stripes
-// are then written straight to HBM, coalesced along the row.
+// are then written straight to HBM, coalesced along the row and past the
+// caches: the submatrices of a chunk are written once, far more than L2 holds,
+// and the CSR rows that neighbouring submatrices read again stay in it (4,096
+// submatrices of about 612 rows: 5.8 -> 4.9 ms, 4.2 TB/s; a large copy 4.7).
 // grid (max_m, nsub), 256 threads; dynamic LDS: 3 m ints.
 // ---------------------------------------------------------------------------
 #define GATHER_BSMAX 6   // largest block size (the plan refuses larger)
@@ -65,14 +68,14 @@ __global__ __launch_bounds__(256) void k_gather(ChunkDev cd, char *ws, GatherArg
     double *Kd = (double *)(ws + M.offK);   // T_J(K) in FP64, or
     float *Kf = (float *)(ws + M.offK);     // in FP32 when the substitution runs in FP32
     auto put_k = [&](int64_t idx, double v) {
-        if (M.kf32) Kf[idx] = (float)v;
-        else Kd[idx] = v;
+        if (M.kf32) __builtin_nontemporal_store((float)v, Kf + idx);
+        else __builtin_nontemporal_store(v, Kd + idx);
     };
     double *Sd = (double *)(ws + M.offL);   // T_J(S) in FP64, or
     float *Sf = (float *)(ws + M.offL);     // in FP32 for the FP32 Cholesky route
     auto put_s = [&](int64_t idx, double v) {
-        if (ga.s_fp32) Sf[idx] = (float)v;
-        else Sd[idx] = v;
+        if (ga.s_fp32) __builtin_nontemporal_store((float)v, Sf + idx);
+        else __builtin_nontemporal_store(v, Sd + idx);
     };
     const int64_t ldk = np + 64, lds = np;
     const int bb = bs * bs;
