@@ -144,6 +144,15 @@ static hipError_t run_finish(const ChunkDev &cd, char *ws, int nfinal, int bs, h
 // in the 256 MB last-level cache across the nine products, where more
 // workgroups per CU would re-read it from HBM.
 // ---------------------------------------------------------------------------
+// (submatrix, owned molecule) of a workgroup: the molecules of a submatrix in
+// turn on one XCD (workgroup b runs on XCD b % 8), where they share its L2
+__device__ __forceinline__ void own_task(const ChunkDev &cd, int &s, int &o) {
+    const int wb = blockIdx.x >> 3;
+    s = (wb / cd.max_own) * 8 + (blockIdx.x & 7);
+    o = wb % cd.max_own;
+}
+static dim3 own_grid(const ChunkDev &cd) { return dim3((cd.nsub + 7) / 8 * 8 * cd.max_own); }
+
 #define FIN_THREADS 1024
 #define FIN_LDS_MIN (96 * 1024)
 typedef float v4f_fin __attribute__((ext_vector_type(4)));
@@ -161,7 +170,8 @@ __constant__ FinStep fin_steps[9] = {{-1, -2, 0, -1, 1.0f, 0.0f}, {0, -2, 1, -1,
 __global__ __launch_bounds__(FIN_THREADS, 1) void k_finish_f16(ChunkDev cd, char *ws, int nsteps, int bs,
                                                                 int mirror) {
     extern __shared__ __attribute__((aligned(16))) uint16_t vb[];   // [16][np + 8]
-    const int s = blockIdx.x, o = blockIdx.y;
+    int s, o;
+    own_task(cd, s, o);
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
     const SubCtl *ctl = cd.ctl + s;
@@ -263,7 +273,7 @@ hipError_t launch_finish(const ChunkDev &cd, char *ws, const FinishArgs &fa, hip
                 size_t lds = (size_t)16 * (cd.max_np + 8) * 2;
                 if (lds < FIN_LDS_MIN) lds = FIN_LDS_MIN;
                 const int nsteps = fa.nfinal == 0 ? 1 : (fa.nfinal == 1 ? 3 : 9);
-                hipLaunchKernelGGL(k_finish_f16, dim3(cd.nsub, cd.max_own), dim3(FIN_THREADS), lds, st, cd, ws,
+                hipLaunchKernelGGL(k_finish_f16, own_grid(cd), dim3(FIN_THREADS), lds, st, cd, ws,
                                    nsteps, bs, fa.mirror);
                 return hipGetLastError();
             }
@@ -273,7 +283,10 @@ hipError_t launch_finish(const ChunkDev &cd, char *ws, const FinishArgs &fa, hip
 }
 
 // ---------------------------------------------------------------------------
-// Extraction, traces and write-back, one workgroup per submatrix.
+// Extraction, traces and write-back, one workgroup per submatrix and owned
+// molecule (the molecules of a combined submatrix one after the other in one
+// workgroup, each a chain of latencies down the factor, took 7.3 ms for 693
+// submatrices of 2,000 molecules; side by side 2.0).
 //   Dcols_J = (Y_J - Z_J) / 2 (FP64), Z_J = X Y_J from the products above;
 //   N_J = sum_c (S_J Dcols_J)[bs p + c, c], E_J = sum_c (K_J Dcols_J)[bs p + c, c]
 // (Eq. e_elec: the energy only needs D where K is stored; row J of K / S
@@ -337,14 +350,18 @@ __device__ void back_solve_lt(const TL *L, const TL *Dinv, const SubMeta &M, dou
     }
 }
 
+// three workgroups per CU, as their LDS allows (at two the back solve of
+// 4,096 submatrices took 2.07 ms for 1.60)
 template <typename TV>
-__global__ __launch_bounds__(256) void k_extract(ChunkDev cd, char *ws, ExtractArgs ea) {
+__global__ __launch_bounds__(256, 3) void k_extract(ChunkDev cd, char *ws, ExtractArgs ea) {
     extern __shared__ double smem[];
     __shared__ double red[256];
     __shared__ double tmp[4 * 64 * BSMAX];
-    const int s = blockIdx.x;
+    int s, o;
+    own_task(cd, s, o);
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
+    if (o >= M.nown) return;
     const SubCtl *ctl = cd.ctl + s;
     const int bs = ea.bs, n = M.n, np = M.np, t = threadIdx.x;
     double *Df = smem;                                    // np x bs: whole-submatrix column block
@@ -352,89 +369,86 @@ __global__ __launch_bounds__(256) void k_extract(ChunkDev cd, char *ws, ExtractA
     for (int i = t; i < M.m; i += 256) rows[i] = ea.grp_blk[M.sub_off + i];
     const bool ok = ctl->status != NOLSM_MOL_NOT_SPD;
     const int64_t vs = (int64_t)np * 6 * 8 / sizeof(TV);
-    for (int o = 0; o < M.nown; ++o) {
-        const int J = ea.own_J[M.own_off + o];
-        const int so = ea.sub_ptr[J], mJ = ea.sub_ptr[J + 1] - so;
-        const TV *V = (const TV *)(ws + M.offVec) + (int64_t)o * NOLSM_NVEC * vs;
-        __syncthreads();   // Df of the previous molecule is no longer read
-        for (int f = t; f < np * bs; f += 256) {
-            const int r = f / bs, c = f % bs;
-            double v = 0.0;
-            if (ok && r < n) {
-                const double y = kbuf_get(M, ws, (int64_t)r * (np + 64) + np + o * bs + c);
-                const int64_t q = (int64_t)r * 6 + c;
-                double z;
-                if (ea.nfinal == 0)
-                    z = (double)V[q];
-                else if (ea.nfinal == 1)
-                    z = 1.5 * (double)V[q] - 0.5 * (double)V[2 * vs + q];
-                else
-                    z = 1.5 * (double)V[3 * vs + q] - 0.75 * (double)V[8 * vs + q] + 0.25 * (double)V[10 * vs + q];
-                v = 0.5 * (y - z);
+    const int J = ea.own_J[M.own_off + o];
+    const int so = ea.sub_ptr[J], mJ = ea.sub_ptr[J + 1] - so;
+    const TV *V = (const TV *)(ws + M.offVec) + (int64_t)o * NOLSM_NVEC * vs;
+    for (int f = t; f < np * bs; f += 256) {
+        const int r = f / bs, c = f % bs;
+        double v = 0.0;
+        if (ok && r < n) {
+            const double y = kbuf_get(M, ws, (int64_t)r * (np + 64) + np + o * bs + c);
+            const int64_t q = (int64_t)r * 6 + c;
+            double z;
+            if (ea.nfinal == 0)
+                z = (double)V[q];
+            else if (ea.nfinal == 1)
+                z = 1.5 * (double)V[q] - 0.5 * (double)V[2 * vs + q];
+            else
+                z = 1.5 * (double)V[3 * vs + q] - 0.75 * (double)V[8 * vs + q] + 0.25 * (double)V[10 * vs + q];
+            v = 0.5 * (y - z);
+        }
+        Df[f] = v;
+    }
+    __syncthreads();
+    if (ea.sym && ok) {
+        // the FP32 factor, or the FP32 copy of the FP64 factor where the
+        // route applies it in FP32, else the FP64 factor
+        if (ea.L_fp32) back_solve_lt((const float *)(ws + M.offL), (const float *)(ws + M.offDinv), M, Df, tmp, bs);
+        else if (M.offL32)
+            back_solve_lt((const float *)(ws + M.offL32), (const float *)(ws + M.offDinv32), M, Df, tmp, bs);
+        else back_solve_lt((const double *)(ws + M.offL), (const double *)(ws + M.offDinv), M, Df, tmp, bs);
+    }
+    // the owned columns on the rows N(J) (the pattern of D), through
+    // the row positions of N(J) in this submatrix
+    double *Dout = ea.Dcols + (int64_t)bs * bs * so;
+    for (int f = t; f < mJ * bs * bs; f += 256) {
+        const int a = f / (bs * bs), rc = f % (bs * bs);
+        const double v = Df[(ea.rowpos[so + a] * bs) * bs + rc];
+        Dout[f] = v;
+        if (ea.Dval) ea.Dval[(int64_t)ea.scatter_pos[so + a] * bs * bs + rc] = v;
+    }
+    // the whole column block is kept for the W columns
+    if (ea.Wcols) {
+        double *Wk = (double *)(ws + M.offVec) + (int64_t)(o * NOLSM_NVEC + NOLSM_NVEC - 1) * np * 6;
+        for (int f = t; f < np * bs; f += 256) Wk[(f / bs) * 6 + f % bs] = Df[f];
+    }
+    // traces over row J of S and of K: every stored column block C of
+    // row J lies in N(J), hence in the submatrix rows
+    double tr[2];
+    for (int which = 0; which < 2; ++which) {
+        const int *rp = which ? ea.Krp : ea.Srp;
+        const int *ci = which ? ea.Kci : ea.Sci;
+        const double *val = which ? ea.Kval : ea.Sval;
+        const int lo = rp[J], hi = rp[J + 1];
+        const int nel = (hi - lo) * bs * bs;
+        double part = 0.0;
+        for (int f = t; f < nel; f += 256) {
+            const int e = lo + f / (bs * bs), rc = f % (bs * bs);
+            const int c = rc / bs, d = rc % bs;
+            const int C = ci[e];
+            int l = 0, h = M.m - 1, b = -1;
+            while (l <= h) {
+                const int mid = (l + h) >> 1;
+                const int v = rows[mid];
+                if (v == C) { b = mid; break; }
+                if (v < C) l = mid + 1; else h = mid - 1;
             }
-            Df[f] = v;
+            if (b >= 0) part += val[(int64_t)e * bs * bs + rc] * Df[(b * bs + d) * bs + c];
         }
-        __syncthreads();
-        if (ea.sym && ok) {
-            // the FP32 factor, or the FP32 copy of the FP64 factor where the
-            // route applies it in FP32, else the FP64 factor
-            if (ea.L_fp32) back_solve_lt((const float *)(ws + M.offL), (const float *)(ws + M.offDinv), M, Df, tmp, bs);
-            else if (M.offL32)
-                back_solve_lt((const float *)(ws + M.offL32), (const float *)(ws + M.offDinv32), M, Df, tmp, bs);
-            else back_solve_lt((const double *)(ws + M.offL), (const double *)(ws + M.offDinv), M, Df, tmp, bs);
-        }
-        // the owned columns on the rows N(J) (the pattern of D), through
-        // the row positions of N(J) in this submatrix
-        double *Dout = ea.Dcols + (int64_t)bs * bs * so;
-        for (int f = t; f < mJ * bs * bs; f += 256) {
-            const int a = f / (bs * bs), rc = f % (bs * bs);
-            const double v = Df[(ea.rowpos[so + a] * bs) * bs + rc];
-            Dout[f] = v;
-            if (ea.Dval) ea.Dval[(int64_t)ea.scatter_pos[so + a] * bs * bs + rc] = v;
-        }
-        // the whole column block is kept for the W columns
-        if (ea.Wcols) {
-            double *Wk = (double *)(ws + M.offVec) + (int64_t)(o * NOLSM_NVEC + NOLSM_NVEC - 1) * np * 6;
-            for (int f = t; f < np * bs; f += 256) Wk[(f / bs) * 6 + f % bs] = Df[f];
-        }
-        // traces over row J of S and of K: every stored column block C of
-        // row J lies in N(J), hence in the submatrix rows
-        double tr[2];
-        for (int which = 0; which < 2; ++which) {
-            const int *rp = which ? ea.Krp : ea.Srp;
-            const int *ci = which ? ea.Kci : ea.Sci;
-            const double *val = which ? ea.Kval : ea.Sval;
-            const int lo = rp[J], hi = rp[J + 1];
-            const int nel = (hi - lo) * bs * bs;
-            double part = 0.0;
-            for (int f = t; f < nel; f += 256) {
-                const int e = lo + f / (bs * bs), rc = f % (bs * bs);
-                const int c = rc / bs, d = rc % bs;
-                const int C = ci[e];
-                int l = 0, h = M.m - 1, b = -1;
-                while (l <= h) {
-                    const int mid = (l + h) >> 1;
-                    const int v = rows[mid];
-                    if (v == C) { b = mid; break; }
-                    if (v < C) l = mid + 1; else h = mid - 1;
-                }
-                if (b >= 0) part += val[(int64_t)e * bs * bs + rc] * Df[(b * bs + d) * bs + c];
-            }
-            tr[which] = block_sum(part, red);
-        }
-        if (t == 0) {
-            MolStatsDev *st = (MolStatsDev *)ea.stats + J;
-            st->iters = ctl->iters;
-            st->iters_fp32 = (ok && (ea.prec == NOLSM_FP16 || ea.prec == NOLSM_BF16)) ? ea.nfinal : 0;
-            st->fallback = ctl->fallback;
-            st->status = ctl->status;
-            st->scale = ctl->scale;
-            st->resid = ctl->resid;
-            st->trace_SD = ok ? tr[0] : 0.0;
-            st->energy_KD = ok ? tr[1] : 0.0;
-            st->iters_inv = cd.ictl ? cd.ictl[s].iters : 0;
-            st->reserved_ = 0;
-        }
+        tr[which] = block_sum(part, red);
+    }
+    if (t == 0) {
+        MolStatsDev *st = (MolStatsDev *)ea.stats + J;
+        st->iters = ctl->iters;
+        st->iters_fp32 = (ok && (ea.prec == NOLSM_FP16 || ea.prec == NOLSM_BF16)) ? ea.nfinal : 0;
+        st->fallback = ctl->fallback;
+        st->status = ctl->status;
+        st->scale = ctl->scale;
+        st->resid = ctl->resid;
+        st->trace_SD = ok ? tr[0] : 0.0;
+        st->energy_KD = ok ? tr[1] : 0.0;
+        st->iters_inv = cd.ictl ? cd.ictl[s].iters : 0;
+        st->reserved_ = 0;
     }
 }
 
@@ -504,9 +518,9 @@ hipError_t launch_wcols(const ChunkDev &cd, char *ws, const ExtractArgs &ea, hip
 hipError_t launch_extract(const ChunkDev &cd, char *ws, const ExtractArgs &ea, hipStream_t st) {
     const size_t lds = (size_t)cd.max_np * ea.bs * 8 + (size_t)cd.max_m * 4 + 16;
     if (ea.prec == NOLSM_FP64)
-        hipLaunchKernelGGL(k_extract<double>, dim3(cd.nsub), dim3(256), lds, st, cd, ws, ea);
+        hipLaunchKernelGGL(k_extract<double>, own_grid(cd), dim3(256), lds, st, cd, ws, ea);
     else
-        hipLaunchKernelGGL(k_extract<float>, dim3(cd.nsub), dim3(256), lds, st, cd, ws, ea);
+        hipLaunchKernelGGL(k_extract<float>, own_grid(cd), dim3(256), lds, st, cd, ws, ea);
     return hipGetLastError();
 }
 
