@@ -10,6 +10,8 @@
 // (on the symmetric route by default as split FP16 products, split16.h);
 // the K buffer (K, then W, then A or A~ and Y) is stored in the type of that
 // arithmetic.
+#include <utility>
+
 #include "dev_common.h"
 #include "kernels.h"
 #include "split16.h"
@@ -269,32 +271,49 @@ __device__ __forceinline__ void mblk_pos(int b, int &bi, int &bj) {
     bi = (b == 3) ? 1 : 0;
     bj = (b == 3) ? 2 : b + 1;
 }
-__device__ void chol16_wave(double v[4], int &bad) {
-    const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
+// The exchanges of these chains, most of them without LDS: a value of one
+// lane for all (v_readlane), a value of lane N of each group of 16 for that
+// group (DPP row_newbcast).
+template <int LANE> __device__ __forceinline__ double lane_get(double x) {
+    const int2 u = __builtin_bit_cast(int2, x);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(u.x, LANE), __builtin_amdgcn_readlane(u.y, LANE)));
+}
+template <int N> __device__ __forceinline__ double group_get(double x) {
+    const int2 u = __builtin_bit_cast(int2, x);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(u.x, 0x150 + N, 0xF, 0xF, true),
+                                                __builtin_amdgcn_mov_dpp(u.y, 0x150 + N, 0xF, 0xF, true)));
+}
+template <int C> __device__ __forceinline__ void chol16_step(double (&v)[4], int &bad, int g, int q) {
+    // A[c][q], equal to A[q][c]: the trailing matrix is updated on both
+    // sides of its diagonal, so it stays symmetric
+    const double rowq = __shfl(v[C >> 2], q + 16 * (C & 3), 64);
+    const double d = lane_get<C + 16 * (C & 3)>(v[C >> 2]);   // A[c][c]
+    bad |= !(d > 0.0);
+    const double piv = sqrt(fmax(d, 1e-300));
+    const double rp = 1.0 / piv;
+    const double lq = rowq * rp;
+    double colr[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        const double d = __shfl(v[c >> 2], c + 16 * (c & 3), 64);   // A[c][c]
-        bad |= !(d > 0.0);
-        const double piv = sqrt(fmax(d, 1e-300));
-        const double rp = 1.0 / piv;
-        double colr[4];
+    for (int e = 0; e < 4; ++e) colr[e] = group_get<C>(v[e]);   // A[g + 4e][c]
 #pragma unroll
-        for (int e = 0; e < 4; ++e) colr[e] = __shfl(v[e], c + 16 * g, 64);   // A[g + 4e][c]
-        // A[c][q], equal to A[q][c]: the trailing matrix is updated on both
-        // sides of its diagonal, so it stays symmetric
-        const double lq = __shfl(v[c >> 2], q + 16 * (c & 3), 64) * rp;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = g + 4 * e;
-            const double lr = colr[e] * rp;
-            if (q == c) {
-                if (r > c) v[e] = lr;
-                else if (r == c) v[e] = piv;
-            } else if (q > c && r > c) {
-                v[e] -= lr * lq;
-            }
+    for (int e = 0; e < 4; ++e) {
+        const int r = g + 4 * e;
+        const double lr = colr[e] * rp;
+        if (q == C) {
+            if (r > C) v[e] = lr;
+            else if (r == C) v[e] = piv;
+        } else if (q > C && r > C) {
+            v[e] -= lr * lq;
         }
     }
+}
+template <int... C> __device__ __forceinline__ void chol16_steps(double (&v)[4], int &bad, int g, int q,
+                                                                 std::integer_sequence<int, C...>) {
+    (chol16_step<C>(v, bad, g, q), ...);
+}
+__device__ void chol16_wave(double (&v)[4], int &bad) {
+    const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
+    chol16_steps(v, bad, g, q, std::make_integer_sequence<int, 16>());
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (g + 4 * e < q) v[e] = 0.0;
@@ -302,22 +321,25 @@ __device__ void chol16_wave(double v[4], int &bad) {
 // M = L^-1 for the lower-triangular 16x16 L in registers: M = I, then for
 // each pivot row p, row p of M is scaled by 1 / L[p][p] (final) and taken
 // off the rows below it, L[r][p] times.
-__device__ void inv16_wave(const double v[4], double m[4]) {
+template <int P> __device__ __forceinline__ void inv16_step(const double (&v)[4], double (&m)[4], int g, int q) {
+    const double lpp = lane_get<P + 16 * (P & 3)>(v[P >> 2]);
+    if (g == (P & 3)) m[P >> 2] /= lpp;
+    const double xq = __shfl(m[P >> 2], q + 16 * (P & 3), 64);   // M[p][q], final
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double lrp = group_get<P>(v[e]);   // L[g + 4e][p]
+        if (g + 4 * e > P) m[e] -= lrp * xq;
+    }
+}
+template <int... P> __device__ __forceinline__ void inv16_steps(const double (&v)[4], double (&m)[4], int g, int q,
+                                                                std::integer_sequence<int, P...>) {
+    (inv16_step<P>(v, m, g, q), ...);
+}
+__device__ void inv16_wave(const double (&v)[4], double (&m)[4]) {
     const int l = threadIdx.x & 63, g = l >> 4, q = l & 15;
 #pragma unroll
     for (int e = 0; e < 4; ++e) m[e] = (g + 4 * e == q) ? 1.0 : 0.0;
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-        const double lpp = __shfl(v[p >> 2], p + 16 * (p & 3), 64);
-        if (g == (p & 3)) m[p >> 2] /= lpp;
-        const double xq = __shfl(m[p >> 2], q + 16 * (p & 3), 64);   // M[p][q], final
-        double lrp[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) lrp[e] = __shfl(v[e], p + 16 * g, 64);   // L[g + 4e][p]
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (g + 4 * e > p) m[e] -= lrp[e] * xq;
-    }
+    inv16_steps(v, m, g, q, std::make_integer_sequence<int, 16>());
 }
 __device__ void chol_inv64_blocked(double (*sA)[LDP], double *Dg, float *Df, int *fail) {
     const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 4, q = l & 15;
