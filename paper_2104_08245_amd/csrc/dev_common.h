@@ -19,6 +19,26 @@ __device__ __forceinline__ uint32_t xcd_task(const uint32_t *list) {
     const uint32_t G = gridDim.x, b = blockIdx.x;
     return list[(b & 7u) * (G >> 3) + (b >> 3)];
 }
+// Launches of several workgroups (parts y < ny) per submatrix: a block of
+// submatrices of one XCD part by part, as many as its CUs run at once (two
+// workgroups each of 32), so that the parts of a submatrix run at the same
+// time there and share its L2, while each part's workgroups follow each
+// other. (An XCD hands workgroups to its engines in turn: with the parts
+// alternating, those that are longer, or return at once, all go to the same
+// engines.)
+__host__ __device__ __forceinline__ int parts_block(int nsub, int ny) {
+    const int per_xcd = (nsub + 7) / 8, b = ny < 8 ? 64 / ny : 8;
+    return per_xcd < b ? per_xcd : b;
+}
+__device__ __forceinline__ void parts_task(int nsub, int ny, int &s, int &y) {
+    const int B = parts_block(nsub, ny), wb = blockIdx.x >> 3, blk = wb / (B * ny), rem = wb - blk * (B * ny);
+    y = rem / B;
+    s = (blk * B + rem - y * B) * 8 + (blockIdx.x & 7);
+}
+static inline dim3 parts_grid(int nsub, int ny) {
+    const int B = parts_block(nsub, ny), per_xcd = (nsub + 7) / 8;
+    return dim3((unsigned)((per_xcd + B - 1) / B * B * 8 * ny));
+}
 __device__ __forceinline__ int task_slot(uint32_t t) { return (int)(t >> 16); }
 __device__ __forceinline__ int task_a(uint32_t t) { return (int)((t >> 8) & 0xFF); }
 __device__ __forceinline__ int task_b(uint32_t t) { return (int)(t & 0xFF); }

@@ -146,6 +146,8 @@ static hipError_t run_finish(const ChunkDev &cd, char *ws, int nfinal, int bs, h
 // ---------------------------------------------------------------------------
 // (submatrix, owned molecule) of a workgroup: the molecules of a submatrix in
 // turn on one XCD (workgroup b runs on XCD b % 8), where they share its L2
+// (up to 32 submatrices molecule by molecule, as parts_task has it, took the
+// finishing of the case below from 5.6 to 6.3 ms)
 __device__ __forceinline__ void own_task(const ChunkDev &cd, int &s, int &o) {
     const int wb = blockIdx.x >> 3;
     s = (wb / cd.max_own) * 8 + (blockIdx.x & 7);

@@ -455,15 +455,29 @@ __device__ void chol_inv64_blocked(double (*sA)[LDP], double *Dg, float *Df, int
     __syncthreads();
 }
 
-// Panel j, diagonal tile: L_jj L_jj^T = S_jj - sum_{k<j} L_jk L_jk^T, and
-// its inverse. One workgroup per submatrix with P > j. A non-positive pivot
-// marks the submatrix NOT_SPD; its later launches then skip it.
+// Panels go in pairs (j, j + 1), j even: every tile of the factor left of
+// them is read once for both, and these reads are what bounds the
+// factorisation (one panel per pass ran at 4.65 TB/s of a large copy's 4.7).
+//
+// LDS slices of 32 columns, rows on distinct banks and 16-byte aligned.
+#define CHOL_BK 32
+template <typename T> struct CholSlice {
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    static constexpr int LD = CHOL_BK + (sizeof(T) == 8 ? 2 : 4), VE = 16 / sizeof(T);
+    static constexpr int AL = CHOL_BK / VE, AR = 256 / AL, AP = 64 / AR;   // lanes a row, rows a pass, passes
+};
+
+// Diagonal block of a pair: L_jj and its inverse from S_jj - sum_{k<j} L_jk
+// L_jk^T, then L_{j+1,j}, then L_{j+1,j+1} and its inverse. One workgroup per
+// submatrix with P > j, three per CU, so that the serial chains of one hide
+// behind the others. A non-positive pivot marks the submatrix NOT_SPD; its
+// later launches then skip it.
 template <typename T>
-__global__ __launch_bounds__(256, 4) void k_chol_diag(ChunkDev cd, char *ws, int j) {
-    // one tile (33 KB in FP64) plus small buffers, and at most 128 VGPRs:
-    // four workgroups share a CU, so that the serial chains of one (the
-    // diagonal blocks) hide behind the others
-    __shared__ T sA[64][LDP];
+__global__ __launch_bounds__(256, 3) void k_chol_diag2(ChunkDev cd, char *ws, int j) {
+    typedef CholSlice<T> C;
+    typedef typename C::vec vec;
+    constexpr int LD = C::LD, TILE = 64 * LDP, SLICES = 2 * 64 * LD;
+    __shared__ __attribute__((aligned(16))) T sm[SLICES > TILE ? SLICES : TILE];
     __shared__ T cb[2][64];
     __shared__ T rd[64];
     __shared__ int fail;
@@ -474,107 +488,264 @@ __global__ __launch_bounds__(256, 4) void k_chol_diag(ChunkDev cd, char *ws, int
     if (j >= M.P || ctl->status != NOLSM_MOL_OK) return;
     T *L = (T *)(ws + M.offL);         // S, factored in place (FP32 route: FP32)
     T *Dinv = (T *)(ws + M.offDinv);
-    const int64_t ld = M.np;
-    auto Lt = [&](int r, int c) { return L + (int64_t)(r * 64) * ld + c * 64; };
-    if (threadIdx.x == 0) fail = 0;
-    AccT<T> acc;
-    g2acc(acc, Lt(j, j), ld);
-    // - L_jk L_jk^T over k < j, tile k + 1 loaded into registers while
-    // tile k is multiplied
-    RegTile<T> pl;
-    if (j > 0) g2r_tile(pl, Lt(j, 0), ld);
-    for (int k = 0; k < j; ++k) {
-        r2s_tile(sA, pl);
-        __syncthreads();
-        if (k + 1 < j) g2r_tile(pl, Lt(j, k + 1), ld);
-        mma64<false, true>(acc, sA, sA, -1.0);
-        __syncthreads();
-    }
-    acc2s(sA, acc);
-    __syncthreads();
-    // FP64 factor applied in FP32: the tile and its inverse also in FP32
+    // FP64 factor applied in FP32: the tiles and inverses also in FP32
     float *L32 = M.offL32 ? (float *)(ws + M.offL32) : nullptr;
-    float *D32 = M.offDinv32 ? (float *)(ws + M.offDinv32) + (int64_t)j * 4096 : nullptr;
-    if constexpr (sizeof(T) == 8) {
-        chol_inv64_blocked(sA, Dinv + (int64_t)j * 4096, D32, &fail);
+    float *D32 = M.offDinv32 ? (float *)(ws + M.offDinv32) : nullptr;
+    const int64_t ld = M.np;
+    const bool two = j + 1 < M.P;
+    T(*sA)[LDP] = (T(*)[LDP])sm;
+    auto Lt = [&](int r, int c) { return L + (int64_t)(r * 64) * ld + c * 64; };
+    auto store = [&](int r, int c) {
+        s2g_tile(Lt(r, c), ld, sA);
+        if (L32) s2g_tile(L32 + (int64_t)(r * 64) * ld + c * 64, ld, sA);
+    };
+    // factor and inverse of diagonal tile i from its accumulators; false: not SPD
+    auto factor = [&](const AccT<T> &acc, int i) -> bool {
+        acc2s(sA, acc);
+        __syncthreads();
+        T *Di = Dinv + (int64_t)i * 4096;
+        float *Df = D32 ? D32 + (int64_t)i * 4096 : nullptr;
+        if constexpr (sizeof(T) == 8) chol_inv64_blocked(sA, Di, Df, &fail);
+        else potrf64_reg(sA, cb, &fail);
         if (fail) {
             if (threadIdx.x == 0) { ctl->status = NOLSM_MOL_NOT_SPD; ctl->done = 1; }
-            return;
+            return false;
         }
-    } else {
-        potrf64_reg(sA, cb, &fail);
-        if (fail) {
-            if (threadIdx.x == 0) { ctl->status = NOLSM_MOL_NOT_SPD; ctl->done = 1; }
-            return;
-        }
-        trinv64_reg(sA, Dinv + (int64_t)j * 4096, rd, cb, D32);
+        if constexpr (sizeof(T) == 4) trinv64_reg(sA, Di, rd, cb, Df);
+        store(i, i);
+        __syncthreads();
+        return true;
+    };
+    const int t = threadIdx.x, ar = t / C::AL, ac = (t % C::AL) * C::VE;
+    const int w = t >> 6, l = t & 63, r0 = (w >> 1) * 32, c0 = (w & 1) * 32, li = l & 15, lk = l >> 4;
+    const T *ra = sm + (r0 + li) * LD + lk, *rb = sm + (c0 + li) * LD + lk;   // second row block: + 64 LD
+    if (t == 0) fail = 0;
+    AccT<T> a00, a10, a11;
+    g2acc(a00, Lt(j, j), ld);
+    if (two) {
+        g2acc(a10, Lt(j + 1, j), ld);
+        g2acc(a11, Lt(j + 1, j + 1), ld);
     }
-    s2g_tile(Lt(j, j), ld, sA);
-    if (L32) s2g_tile(L32 + (int64_t)(j * 64) * ld + j * 64, ld, sA);
+    // the sums over the columns left of j, the next slice of rows j, j + 1 in
+    // registers while this one is multiplied
+    vec px[2][C::AP];
+    auto fetch = [&](int q) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+            if (x == 0 || two)
+#pragma unroll
+                for (int p = 0; p < C::AP; ++p)
+                    px[x][p] = *(const vec *)(Lt(j + x, 0) + (int64_t)(ar + p * C::AR) * ld + q * CHOL_BK + ac);
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+            if (x == 0 || two)
+#pragma unroll
+                for (int p = 0; p < C::AP; ++p) *(vec *)(sm + (x * 64 + ar + p * C::AR) * LD + ac) = px[x][p];
+    };
+    const int nq = j * 64 / CHOL_BK;
+    if (nq > 0) {
+        fetch(0);
+        stash();
+        __syncthreads();
+    }
+    for (int q = 0; q < nq; ++q) {
+        if (q + 1 < nq) fetch(q + 1);
+        __builtin_amdgcn_sched_barrier(0);   // ahead of the products, not next to their use
+#pragma unroll 4
+        for (int k = 0; k < CHOL_BK; k += 4) {
+            T x[2], y[2], u[2], v[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                x[m] = -ra[m * 16 * LD + k];
+                y[m] = rb[m * 16 * LD + k];
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int n = 0; n < 2; ++n) a00.c[m][n] = Mfma16<T>::mma(x[m], y[n], a00.c[m][n]);
+            if (two) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    u[m] = -ra[(64 + m * 16) * LD + k];
+                    v[m] = rb[(64 + m * 16) * LD + k];
+                }
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        a10.c[m][n] = Mfma16<T>::mma(u[m], y[n], a10.c[m][n]);
+                        a11.c[m][n] = Mfma16<T>::mma(u[m], v[n], a11.c[m][n]);
+                    }
+            }
+        }
+        __syncthreads();
+        if (q + 1 < nq) {
+            stash();
+            __syncthreads();
+        }
+    }
+    if (!factor(a00, j) || !two) return;
+    // L_{j+1,j} = (its sum) L_jj^-T, by halves of 32 columns of both
+    AccT<T> o;
+    acc_zero(o);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if ((w & 1) == h) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sm[acc_row<T>(m, e) * LD + n * 16 + li] = a10.c[m][n][e];
+        }
+#pragma unroll
+        for (int p = 0; p < C::AP; ++p)
+            *(vec *)(sm + (64 + ar + p * C::AR) * LD + ac) =
+                *(const vec *)(Dinv + (int64_t)j * 4096 + (ar + p * C::AR) * 64 + h * 32 + ac);
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < CHOL_BK; k += 4)
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+                    o.c[m][n] = Mfma16<T>::mma(ra[m * 16 * LD + k], rb[(64 + n * 16) * LD + k], o.c[m][n]);
+        __syncthreads();
+    }
+    acc2s(sA, o);
+    __syncthreads();
+    store(j + 1, j);
+    mma64<false, true>(a11, sA, sA, -1.0);
+    __syncthreads();
+    factor(a11, j + 1);
 }
 
-// Panel j below the diagonal: L_ij = (S_ij - sum_{k<j} L_ik L_jk^T) L_jj^-T
-// for CHOL_PR row tiles i per workgroup, which share each L_jk load; the
-// row tiles of a panel run in parallel. Grid: (submatrix, block of rows).
-#define CHOL_PR 4
+// Panels j, j + 1 below their diagonal block: L_ij = (S_ij - sum_{k<j} L_ik
+// L_jk^T) L_jj^-T and L_{i,j+1} alike (its sum runs over k <= j), for CHOL_PR
+// row tiles i per workgroup. The sums run in slices of 32 columns, the next
+// slice of the CHOL_PR + 2 row blocks in registers while this one is
+// multiplied from LDS. The workgroups of a submatrix share the rows j, j + 1
+// through one XCD's L2.
+// With the diagonal launches, one panel at a time: 12.8 ms for 4,096
+// submatrices of about 612 rows, 28.8 for a slab of 2,048 (340 to 1,520 rows);
+// now 11.9 and 25.9.
+#define CHOL_PR 2
 template <typename T, int OCC>
-__global__ __launch_bounds__(256, OCC) void k_chol_panel(ChunkDev cd, char *ws, int j) {
-    __shared__ T sA[64][LDP];
-    __shared__ T sB[64][LDP];
-    const int s = blockIdx.x;
+__global__ __launch_bounds__(256, OCC) void k_chol_panel2(ChunkDev cd, char *ws, int j, int ny) {
+    typedef CholSlice<T> C;
+    typedef typename C::vec vec;
+    constexpr int BK = CHOL_BK, LD = C::LD, VE = C::VE, AL = C::AL, AR = C::AR, AP = C::AP, NX = CHOL_PR + 2;
+    constexpr int SLICE = 64 * LD * NX, TILES = 2 * 64 * LDP;
+    __shared__ __attribute__((aligned(16))) T sm[SLICE > TILES ? SLICE : TILES];
+    int s, y;
+    parts_task(cd.nsub, ny, s, y);
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
-    const int P = M.P, i0 = j + 1 + (int)blockIdx.y * CHOL_PR;
+    const int P = M.P, i0 = j + 2 + y * CHOL_PR;
     if (i0 >= P || cd.ctl[s].status != NOLSM_MOL_OK) return;
     T *L = (T *)(ws + M.offL);
     const T *Dinv = (const T *)(ws + M.offDinv);
     const int64_t ld = M.np;
     auto Lt = [&](int r, int c) { return L + (int64_t)(r * 64) * ld + c * 64; };
     const int nr = min(CHOL_PR, P - i0);
-    AccT<T> acc[CHOL_PR];
+    AccT<T> acc[CHOL_PR][2];
 #pragma unroll
     for (int r = 0; r < CHOL_PR; ++r)
-        if (r < nr) g2acc(acc[r], Lt(i0 + r, j), ld);
-    // - L_ik L_jk^T over k < j: the row-j tile per k, and the row tiles one
-    // (k, r) step ahead in registers while the current one is multiplied
-    RegTile<T> pl;
-    if (j > 0) g2r_tile(pl, Lt(i0, 0), ld);
-    for (int k = 0; k < j; ++k) {
-        g2s_tile(sB, Lt(j, k), ld);
-        r2s_tile(sA, pl);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            g2acc(acc[r][c], Lt(i0 + (r < nr ? r : 0), j + c), ld);   // a row past the matrix repeats the first
+    const int t = threadIdx.x, ar = t / AL, ac = (t % AL) * VE;
+    const int w = t >> 6, l = t & 63, r0 = (w >> 1) * 32, c0 = (w & 1) * 32, li = l & 15, lk = l >> 4;
+    // slice q: columns 32 q .. of the row tiles (negated), then of rows j, j + 1
+    vec px[NX][AP];
+    auto fetch = [&](int q) {
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const int row = x < CHOL_PR ? i0 + (x < nr ? x : 0) : j + x - CHOL_PR;
+            const T *g = Lt(row, 0) + (int64_t)ar * ld + q * BK + ac;
+#pragma unroll
+            for (int p = 0; p < AP; ++p) px[x][p] = *(const vec *)(g + (int64_t)p * AR * ld);
+        }
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int x = 0; x < NX; ++x)
+#pragma unroll
+            for (int p = 0; p < AP; ++p)
+                *(vec *)(sm + (x * 64 + ar + p * AR) * LD + ac) = x < CHOL_PR ? -px[x][p] : px[x][p];
+    };
+    const T *ra = sm + (r0 + li) * LD + lk, *rb = sm + (CHOL_PR * 64 + c0 + li) * LD + lk;
+    const int nq = j * 64 / BK;
+    if (nq > 0) {
+        fetch(0);
+        stash();
         __syncthreads();
+    }
+    for (int q = 0; q < nq; ++q) {
+        if (q + 1 < nq) fetch(q + 1);
+        __builtin_amdgcn_sched_barrier(0);   // ahead of the products, not next to their use
+#pragma unroll
+        for (int k = 0; k < BK; k += 4) {
+            T a[CHOL_PR][2], b[2][2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int n = 0; n < 2; ++n) b[c][n] = rb[(c * 64 + n * 16) * LD + k];
+#pragma unroll
+            for (int r = 0; r < CHOL_PR; ++r)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) a[r][m] = ra[(r * 64 + m * 16) * LD + k];
+#pragma unroll
+            for (int r = 0; r < CHOL_PR; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int n = 0; n < 2; ++n)
+                            acc[r][c].c[m][n] = Mfma16<T>::mma(a[r][m], b[c][n], acc[r][c].c[m][n]);
+        }
+        __syncthreads();
+        if (q + 1 < nq) {
+            stash();
+            __syncthreads();
+        }
+    }
+    T(*sA)[LDP] = (T(*)[LDP])sm, (*sB)[LDP] = (T(*)[LDP])(sm + 64 * LDP);
+    // (sum of column c) Dinv_{j+c}^T for every row tile, stored and kept
+    auto column = [&](int c) {
+        g2s_tile(sB, Dinv + (int64_t)(j + c) * 4096, 64);
 #pragma unroll
         for (int r = 0; r < CHOL_PR; ++r) {
             if (r < nr) {
-                const bool last_r = (r + 1 == nr);
-                const int kn = last_r ? k + 1 : k, rn = last_r ? 0 : r + 1;
-                if (kn < j) g2r_tile(pl, Lt(i0 + rn, kn), ld);
-                mma64<false, true>(acc[r], sA, sB, -1.0);
+                acc2s(sA, acc[r][c]);
                 __syncthreads();
-                if (!last_r) {
-                    r2s_tile(sA, pl);
-                    __syncthreads();
-                }
+                acc_zero(acc[r][c]);
+                mma64<false, true>(acc[r][c], sA, sB);
+                __syncthreads();
+                acc2s(sA, acc[r][c]);
+                __syncthreads();
+                s2g_tile(Lt(i0 + r, j + c), ld, sA);
+                if (M.offL32) s2g_tile((float *)(ws + M.offL32) + (int64_t)((i0 + r) * 64) * ld + (j + c) * 64, ld, sA);
+                __syncthreads();
             }
         }
-    }
-    g2s_tile(sB, Dinv + (int64_t)j * 4096, 64);
+    };
+    column(0);
+    // column j + 1 also takes off L_ij L_{j+1,j}^T
+    g2s_tile(sB, Lt(j + 1, j), ld);
 #pragma unroll
     for (int r = 0; r < CHOL_PR; ++r) {
         if (r < nr) {
-            acc2s(sA, acc[r]);
+            acc2s(sA, acc[r][0]);
             __syncthreads();
-            AccT<T> o;
-            acc_zero(o);
-            mma64<false, true>(o, sA, sB);   // acc L_jj^-T
-            __syncthreads();
-            acc2s(sA, o);
-            __syncthreads();
-            s2g_tile(Lt(i0 + r, j), ld, sA);
-            if (M.offL32) s2g_tile((float *)(ws + M.offL32) + (int64_t)((i0 + r) * 64) * ld + j * 64, ld, sA);
+            mma64<false, true>(acc[r][1], sA, sB, -1.0);
             __syncthreads();
         }
     }
+    column(1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1074,11 +1245,11 @@ __global__ __launch_bounds__(256, OCC) void k_subst_hl(ChunkDev cd, char *ws) {
 // of row pair c - 1 need its column tiles of the launch before; they come
 // first in that row pair's workgroup (p = c - 1): (i, i), (i, i + 1),
 // (i + 1, i + 1), in that order (row i + 1 needs X_{i+1,i} = X_{i,i+1}^T).
-// The row pairs of a submatrix run side by side on one XCD, and its L2 serves
-// the two rows of the factor to all of them. By row pairs (one workgroup per
+// The row pairs of a submatrix share the two rows of the factor through one
+// XCD's L2. By row pairs (one workgroup per
 // submatrix and launch) every launch read the factor's lower triangle again
-// and few workgroups were in flight: 8.1 -> 7.3 ms for 4,096 submatrices of
-// about 612 rows, 21.7 -> 14.7 ms for a slab of 2,048 (340 to 1,520 rows).
+// and few workgroups were in flight: 8.1 -> 7.1 ms for 4,096 submatrices of
+// about 612 rows, 21.7 -> 14.4 ms for a slab of 2,048 (340 to 1,520 rows).
 template <int OCC>
 __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, int c) {
     const double mu = ((const WsHeader *)ws)->mu;
@@ -1087,14 +1258,9 @@ __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, 
     __shared__ __attribute__((aligned(16))) HLTile sL;    // L_jk or Dinv_j: B[k][n] = sL(n, k)
     __shared__ float sF[64][LDP];
     __shared__ double red[256];
-    // workgroup b runs on XCD b % 8: the c row pairs of a submatrix in turn
-    // there. An XCD hands workgroups to its engines and CUs in turn, so for an
-    // even c the order turns with the submatrix: with the one of the diagonal
-    // tiles (the longest) always first a few CUs got all of those (3700 us for
-    // 2590 at c = 4, 4,096 submatrices of about 612 rows; for an odd c first
-    // is best, 1650 us for 2010 at c = 9 on the slab).
-    const int wb = blockIdx.x >> 3, q = wb / c, s = q * 8 + (blockIdx.x & 7);
-    const int p = (c & 1) ? c - 1 - wb % c : (wb + q) % c;
+    int s, y;
+    parts_task(cd.nsub, c, s, y);
+    const int p = c - 1 - y;   // the one with the diagonal tiles, the longest, first
     if (s >= cd.nsub) return;
     const SubMeta M = cd.meta[s];
     if (cd.ctl[s].status != NOLSM_MOL_OK) return;
@@ -1529,22 +1695,25 @@ hipError_t launch_gather(const ChunkDev &cd, char *ws, const GatherArgs &ga, hip
     hipLaunchKernelGGL(k_gather, dim3(cd.max_m, cd.nsub), dim3(256), lds, st, cd, ws, ga);
     return hipGetLastError();
 }
-// Cholesky of every submatrix of the chunk, left-looking by 64-column panels:
-// per panel a diagonal launch and a launch of the tiles below it.
-hipError_t launch_chol(const ChunkDev &cd, char *ws, bool fp32, hipStream_t st) {
+// Cholesky of every submatrix of the chunk, left-looking by pairs of
+// 64-column panels: per pair a launch of its diagonal block and a launch of
+// the tiles below it.
+template <typename T>
+static hipError_t run_chol(const ChunkDev &cd, char *ws, hipStream_t st) {
     const int pmax = cd.max_np / 64;
-    for (int j = 0; j < pmax; ++j) {
-        if (fp32) hipLaunchKernelGGL(k_chol_diag<float>, dim3(cd.nsub), dim3(256), 0, st, cd, ws, j);
-        else hipLaunchKernelGGL(k_chol_diag<double>, dim3(cd.nsub), dim3(256), 0, st, cd, ws, j);
+    for (int j = 0; j < pmax; j += 2) {
+        hipLaunchKernelGGL(k_chol_diag2<T>, dim3(cd.nsub), dim3(256), 0, st, cd, ws, j);
         LAUNCH_CHECK();
-        const int rows = pmax - 1 - j;
+        const int rows = pmax - 2 - j;
         if (rows <= 0) continue;
-        const dim3 grid(cd.nsub, (rows + CHOL_PR - 1) / CHOL_PR);
-        if (fp32) hipLaunchKernelGGL((k_chol_panel<float, 3>), grid, dim3(256), 0, st, cd, ws, j);
-        else hipLaunchKernelGGL((k_chol_panel<double, 2>), grid, dim3(256), 0, st, cd, ws, j);
+        const int ny = (rows + CHOL_PR - 1) / CHOL_PR;
+        hipLaunchKernelGGL((k_chol_panel2<T, 2>), parts_grid(cd.nsub, ny), dim3(256), 0, st, cd, ws, j, ny);
         LAUNCH_CHECK();
     }
     return hipSuccess;
+}
+hipError_t launch_chol(const ChunkDev &cd, char *ws, bool fp32, hipStream_t st) {
+    return fp32 ? run_chol<float>(cd, ws, st) : run_chol<double>(cd, ws, st);
 }
 hipError_t launch_subst_sym(const ChunkDev &cd, char *ws, bool fp32, bool split16, hipStream_t st) {
     const bool hl = fp32 && split16;
@@ -1563,7 +1732,7 @@ hipError_t launch_subst_sym(const ChunkDev &cd, char *ws, bool fp32, bool split1
     const int pmax = cd.max_np / 64;
     if (hl) {
         for (int c = 1; c <= (pmax + 1) / 2; ++c) {
-            hipLaunchKernelGGL(k_rsolve2_hl<2>, dim3((cd.nsub + 7) / 8 * 8 * c), dim3(256), 0, st, cd, ws, c);
+            hipLaunchKernelGGL(k_rsolve2_hl<2>, parts_grid(cd.nsub, c), dim3(256), 0, st, cd, ws, c);
             LAUNCH_CHECK();
         }
         return hipSuccess;
