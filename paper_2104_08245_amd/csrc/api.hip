@@ -254,7 +254,7 @@ static int enqueue_solve(const nolsm_plan *pl, const BatchArgs &b, const LaunchA
         if ((e = launch_wcols(cd, ws, A.ea, st)) != hipSuccess) return hip_fail(e, "W launch");
     }
     if (prof) {
-        prof->n_ns += 2 * o.max_iter;
+        prof->n_ns += ns_launches(cd, A.na);
         prof->n_fin += finish_launches(A.fa);
     }
     return NOLSM_OK;

@@ -338,9 +338,93 @@ __device__ __forceinline__ void scan_tasks(const ChunkDev &cd, const uint32_t *t
     }
 }
 
+// The iterations from `it0` on of a small chunk as one launch: its workgroups
+// scan their tasks as above and work on every submatrix that still iterates
+// until it is done. What bounds the late launches of a small chunk is their
+// number: 48 (FP16) or 60 (FP64) a chunk, 2.5 to 4.5 us each, when all is
+// converged (64 submatrices of about 350 rows: 834 -> 583 us of iteration in
+// FP16, 1402 -> 1166 us in FP64).
+//
+// A submatrix' tiles of both halves of every remaining iteration are handed
+// out in order by a counter (rest_next); a tile of one half starts when all
+// tiles of the half before are counted as complete (rest_fin). A workgroup
+// holds one uncounted half at a time and counts it before it waits for the
+// next, so it only ever waits for lower numbers, which running workgroups
+// hold: the lowest open one never waits, and every wait ends whatever share
+// of the grid is resident. tile(a, b, it, mode) runs one tile; the tiles of a
+// submatrix are ncol columns of bstep per tile row, or (SYM) its upper tiles.
+// Which workgroup runs a tile does not change its result.
+template <bool SYM, typename Tile>
+__device__ __forceinline__ void rest_of(SubCtl *ctl, int nt, int bstep, int it0, int max_iter, Tile tile) {
+    __shared__ int next_s;
+    const int ncol = (nt + bstep - 1) / bstep, ntile = SYM ? nt * (nt + 1) / 2 : nt * ncol;
+    int mine = 0, last = -1;   // tiles run and not yet counted, their half
+    for (;;) {
+        // one block of thread 0 a turn, with a barrier on either side of it:
+        // no branch on the thread leads from the end of a turn to the next,
+        // so no wave goes round the loop without its first lane
+        if (threadIdx.x == 0) {
+            int k = __hip_atomic_fetch_add(&ctl->rest_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int half = k / ntile;
+            if (half != last) {
+                // the tiles of the half before, written back once for all XCDs
+                if (mine) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the write-back too
+                    __hip_atomic_fetch_add(&ctl->rest_fin, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (half >= 2 * (max_iter - it0)) k = -1;
+                while (k >= 0) {
+                    // `done` after rest_fin: the half that set it then shows
+                    // it. (No acquire here: every turn of the wait would
+                    // empty the L2 that the other workgroups work from.)
+                    const bool ready =
+                        __hip_atomic_load(&ctl->rest_fin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= half * ntile;
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    if (__hip_atomic_load(&ctl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) k = -1;
+                    else if (ready) break;
+                    else __builtin_amdgcn_s_sleep(8);
+                }
+            }
+            next_s = k;
+        }
+        __syncthreads();
+        const int k = __builtin_amdgcn_readfirstlane(next_s);
+        if (k < 0) break;
+        const int half = k / ntile, x = k - half * ntile;
+        if (half != last) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // what other workgroups have written, on any XCD
+            last = half;
+            mine = 0;
+        }
+        ++mine;
+        int a = 0, b = x;
+        if (SYM) {
+            while (b >= nt - a) b -= nt - a, ++a;
+            b += a;
+        } else {
+            a = x / ncol;
+            b = (x - a * ncol) * bstep;
+        }
+        tile(a, b, it0 + (half >> 1), 1 + (half & 1));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // each wave: its stores have reached L2
+        __syncthreads();
+    }
+    __syncthreads();
+}
 template <typename T, int NC>
 __global__ __launch_bounds__(256, 2) void k_ns64_tail(ChunkDev cd, char *ws, NsArgs na, int it, int mode) {
     scan_tasks(cd, cd.t_ns, cd.n_ns, [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
+}
+
+template <typename T, int NC>
+__global__ __launch_bounds__(256, 2) void k_ns64_rest(ChunkDev cd, char *ws, NsArgs na, int it0) {
+    scan_tasks(cd, cd.t_ns, cd.n_ns, [&](uint32_t task) {
+        const int s = task_slot(task);
+        rest_of<false>(cd.ctl + s, cd.meta[s].np / 64, NC / 2, it0, na.max_iter, [&](int a, int b, int it, int mode) {
+            ns64_tile<T, NC>(cd, NOLSM_TASK(s, a, b), ws, na, it, mode);
+        });
+    });
 }
 
 template <typename T, int NC>
@@ -529,12 +613,36 @@ __global__ __launch_bounds__(256, 2) void k_ns_lp_tail(ChunkDev cd, const uint32
                                                     NsArgs na, int it, int mode) {
     scan_tasks(cd, tasks, ntask, [&](uint32_t task) { ns_tile<T, BM, SYM>(cd, task, ws, na, it, mode); });
 }
+
+template <typename T, int BM, bool SYM>
+__global__ __launch_bounds__(256, 2) void k_ns_lp_rest(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws,
+                                                    NsArgs na, int it0) {
+    scan_tasks(cd, tasks, ntask, [&](uint32_t task) {
+        const int s = task_slot(task);
+        rest_of<SYM>(cd.ctl + s, (cd.meta[s].np + BM - 1) / BM, 1, it0, na.max_iter,
+                     [&](int a, int b, int it, int mode) {
+                         ns_tile<T, BM, SYM>(cd, NOLSM_TASK(s, a, b), ws, na, it, mode);
+                     });
+    });
+}
 // iterations from this one on take the scanning launch (FP64 / FP32, which
 // iterate longer: from the second one on; 64 launches after convergence then
 // take 4 us each instead of 75 on 512 submatrices of about 612 rows)
 #define NS_TAIL_IT 16
 #define NS64_TAIL_IT 18
-// its grid: four scanning workgroups per CU (2 x pgrid), at most one per task
+// and in a small chunk from these on one launch runs what is left. Where
+// submatrices do still iterate, a tile behind a counter takes longer than in
+// a launch of its own (every half writes back and empties the L2s), the more
+// so the more of them: 216 submatrices of about 600 rows, all of them
+// iterating, take 433 against 345 us an iteration (FP16), which the launches
+// saved outweigh up to two such iterations, 64 of about 350 rows 61 against 32
+// us, up to seven (FP64 127 against 63, up to four: so it starts later
+// there); 1000 of about 600 rows 1940 against 1490 us, with 1% to gain. Hence
+// chunks of at most eight tasks per workgroup of pgrid.
+#define NS_REST_IT 16
+#define NS64_REST_IT 22
+static bool rest_chunk(const NsArgs &na, int ntask) { return ntask <= 8 * na.pgrid; }
+// grid of both: four scanning workgroups per CU (2 x pgrid), at most one per task
 static int scan_grid(const NsArgs &na, int ntask) {
     const int g = (2 * na.pgrid < ntask ? 2 * na.pgrid : ntask) / 8 * 8;
     return g < 8 ? 8 : g;
@@ -550,31 +658,27 @@ static int persistent_grid(const NsArgs &na, int ntask) {
     return g < 8 ? 8 : g;
 }
 
+template <typename T, int BM, bool SYM>
+static void launch_lp(const ChunkDev &cd, const uint32_t *tasks, int ntask, char *ws, const NsArgs &na, int it, int mode,
+                      hipStream_t st) {
+    if (ntask <= 0) return;
+    if (na.persistent)
+        hipLaunchKernelGGL((k_ns_lp_pq<T, BM, SYM>), dim3(persistent_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask,
+                           launch_queue(cd, it, mode, BM == 64), ws, na, it, mode);
+    else if (it < NS_TAIL_IT)
+        hipLaunchKernelGGL((k_ns_lp<T, BM, SYM>), dim3(ntask), dim3(256), 0, st, cd, tasks, ws, na, it, mode);
+    else if (it < NS_REST_IT || !rest_chunk(na, ntask))
+        hipLaunchKernelGGL((k_ns_lp_tail<T, BM, SYM>), dim3(scan_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+                           na, it, mode);
+    else if (it == NS_REST_IT && mode == 1)
+        hipLaunchKernelGGL((k_ns_lp_rest<T, BM, SYM>), dim3(scan_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+                           na, it);
+}
 template <typename T, bool SYM>
 static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode, hipStream_t st) {
     na.nt_out = lp_nt_out(cd.n_ns, na.pgrid);
-    if (na.persistent) {
-        if (cd.n_ns > 0)
-            hipLaunchKernelGGL((k_ns_lp_pq<T, 128, SYM>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd,
-                               cd.t_ns, cd.n_ns, launch_queue(cd, it, mode, 0), ws, na, it, mode);
-        if (cd.n_ns64 > 0)
-            hipLaunchKernelGGL((k_ns_lp_pq<T, 64, SYM>), dim3(persistent_grid(na, cd.n_ns64)), dim3(256), 0, st, cd,
-                               cd.t_ns64, cd.n_ns64, launch_queue(cd, it, mode, 1), ws, na, it, mode);
-        return;
-    }
-    if (it >= NS_TAIL_IT) {
-        if (cd.n_ns > 0)
-            hipLaunchKernelGGL((k_ns_lp_tail<T, 128, SYM>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.t_ns,
-                               cd.n_ns, ws, na, it, mode);
-        if (cd.n_ns64 > 0)
-            hipLaunchKernelGGL((k_ns_lp_tail<T, 64, SYM>), dim3(scan_grid(na, cd.n_ns64)), dim3(256), 0, st, cd, cd.t_ns64,
-                               cd.n_ns64, ws, na, it, mode);
-        return;
-    }
-    if (cd.n_ns > 0)
-        hipLaunchKernelGGL((k_ns_lp<T, 128, SYM>), dim3(cd.n_ns), dim3(256), 0, st, cd, cd.t_ns, ws, na, it, mode);
-    if (cd.n_ns64 > 0)
-        hipLaunchKernelGGL((k_ns_lp<T, 64, SYM>), dim3(cd.n_ns64), dim3(256), 0, st, cd, cd.t_ns64, ws, na, it, mode);
+    launch_lp<T, 128, SYM>(cd, cd.t_ns, cd.n_ns, ws, na, it, mode, st);
+    launch_lp<T, 64, SYM>(cd, cd.t_ns64, cd.n_ns64, ws, na, it, mode, st);
 }
 
 template <typename T, int NC>
@@ -582,10 +686,12 @@ static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, in
     if (na.persistent)
         hipLaunchKernelGGL((k_ns64_pq<T, NC>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.n_ns,
                            launch_queue(cd, it, mode, 0), ws, na, it, mode);
-    else if (it >= NS64_TAIL_IT)
-        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
-    else
+    else if (it < NS64_TAIL_IT)
         hipLaunchKernelGGL((k_ns64<T, NC>), dim3(cd.n_ns), dim3(256), 0, st, cd, ws, na, it, mode);
+    else if (it < NS64_REST_IT || !rest_chunk(na, cd.n_ns))
+        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
+    else if (it == NS64_REST_IT && mode == 1)
+        hipLaunchKernelGGL((k_ns64_rest<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it);
 }
 template <typename T>
 static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
@@ -612,6 +718,14 @@ hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// launches that max_iter iterations of a chunk take (of each of its tile sizes)
+int ns_launches(const ChunkDev &cd, const NsArgs &na) {
+    const bool lp = na.prec == NOLSM_FP16 || na.prec == NOLSM_BF16;
+    const int rest = lp ? NS_REST_IT : NS64_REST_IT;
+    const bool one = !na.persistent && rest_chunk(na, cd.n_ns) && rest_chunk(na, cd.n_ns64);
+    return one && na.max_iter > rest ? 2 * rest + 1 : 2 * na.max_iter;
 }
 
 // symmetric route, after the last iteration: the returned iterates whole

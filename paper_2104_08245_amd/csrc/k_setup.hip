@@ -1679,6 +1679,7 @@ __global__ void k_init_ctl(ChunkDev cd) {
     if (threadIdx.x == 0) {
         c->done = 0; c->iters = 0; c->status = NOLSM_MOL_OK; c->fallback = 0; c->restart_at = -1;
         c->scale = 0; c->scale_g = 0; c->resid = 0; c->kmax = 0;
+        c->rest_next = 0; c->rest_fin = 0;
     }
     for (int i = threadIdx.x; i < NOLSM_MAX_ITER_CAP; i += blockDim.x) c->rhist[i] = 0.0;
     if (s == 0)

@@ -97,6 +97,7 @@ hipError_t launch_trace_sums(const void *stats, int32_t nb, char *ws, hipStream_
 hipError_t launch_bounds(const ChunkDev &cd, char *ws, const BoundsArgs &ba, int prec, hipStream_t st);
 hipError_t launch_convert(const ChunkDev &cd, char *ws, int prec, int use_scale_g, int sym, hipStream_t st);
 hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it, hipStream_t st);
+int ns_launches(const ChunkDev &cd, const NsArgs &na);
 hipError_t launch_ns_mirror(const ChunkDev &cd, char *ws, hipStream_t st);
 hipError_t launch_finish(const ChunkDev &cd, char *ws, const FinishArgs &fa, hipStream_t st);
 hipError_t launch_extract(const ChunkDev &cd, char *ws, const ExtractArgs &ea, hipStream_t st);

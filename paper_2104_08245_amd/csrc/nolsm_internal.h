@@ -58,7 +58,8 @@ struct SubCtl {
     int32_t fallback;   // Gershgorin restart used
     int32_t restart_at; // iteration of the restart, -1 if none
     uint32_t kmax;      // bits of max |T_J(K)| (FP32, non-negative), from the gather
-    int32_t pad_[2];
+    int32_t rest_next;  // k_ns_rest: tiles handed out
+    int32_t rest_fin;   // and tiles whose results are complete
     double scale;       // c_J actually used
     double scale_g;     // Gershgorin scale 1/rho_G
     double resid;       // residual of the returned iterate
