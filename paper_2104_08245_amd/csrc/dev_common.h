@@ -43,6 +43,41 @@ __device__ __forceinline__ int task_slot(uint32_t t) { return (int)(t >> 16); }
 __device__ __forceinline__ int task_a(uint32_t t) { return (int)((t >> 8) & 0xFF); }
 __device__ __forceinline__ int task_b(uint32_t t) { return (int)(t & 0xFF); }
 
+// Late iterations, when most submatrices have converged: a small grid in
+// which every workgroup scans its share of its XCD's task segment, 256
+// tasks at a time (one per thread), keeps the tasks whose submatrix is still
+// iterating and runs those tiles. A launch after convergence then costs one
+// scan instead of one dispatched workgroup per tile. The order in which the
+// kept tiles run does not matter: each writes only its own outputs.
+template <typename Open, typename Run>
+__device__ __forceinline__ void scan_tasks(const uint32_t *tasks, int ntask, Open open, Run run) {
+    __shared__ uint32_t kept[256];
+    __shared__ int nkept;
+    const int x = blockIdx.x & 7, seg = ntask >> 3, g8 = gridDim.x >> 3, wb = blockIdx.x >> 3;
+    const int span = (seg + g8 - 1) / g8, lo = wb * span, hi = min(seg, lo + span);
+    for (int i0 = lo; i0 < hi; i0 += 256) {
+        if (threadIdx.x == 0) nkept = 0;
+        __syncthreads();
+        const int i = i0 + (int)threadIdx.x;
+        if (i < hi) {
+            const uint32_t task = tasks[x * seg + i];
+            if (task != NOLSM_TASK_NONE && open(task_slot(task))) kept[atomicAdd(&nkept, 1)] = task;
+        }
+        __syncthreads();
+        const int nk = nkept;
+        for (int k = 0; k < nk; ++k) {
+            run(kept[k]);
+            __syncthreads();   // its LDS is free again
+        }
+        __syncthreads();
+    }
+}
+// its grid: four scanning workgroups per CU (pgrid is two), at most one per task
+__host__ __forceinline__ int scan_grid(int pgrid, int ntask) {
+    const int g = (2 * pgrid < ntask ? 2 * pgrid : ntask) / 8 * 8;
+    return g < 8 ? 8 : g;
+}
+
 // ---------------------------------------------------------------------------
 // 64x64 tiles on the matrix cores, 256 threads, in FP64
 // (v_mfma_f64_16x16x4_f64) or FP32 (v_mfma_f32_16x16x4_f32); the global

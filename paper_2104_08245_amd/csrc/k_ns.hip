@@ -308,38 +308,13 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64(ChunkDev c
     ns64_tile<T, NC>(cd, xcd_task(cd.t_ns), ws, na, it, mode);
 }
 
-// Late iterations, when most submatrices have converged: a small grid in
-// which every workgroup scans its share of its XCD's task segment, 256
-// tasks at a time (one per thread), keeps the tasks whose submatrix is still
-// iterating and runs those tiles. A launch after convergence then costs one
-// scan instead of one dispatched workgroup per tile. The order in which the
-// kept tiles run does not matter: each writes only its own outputs.
-template <typename Run>
-__device__ __forceinline__ void scan_tasks(const ChunkDev &cd, const uint32_t *tasks, int ntask, Run run) {
-    __shared__ uint32_t kept[256];
-    __shared__ int nkept;
-    const int x = blockIdx.x & 7, seg = ntask >> 3, g8 = gridDim.x >> 3, wb = blockIdx.x >> 3;
-    const int span = (seg + g8 - 1) / g8, lo = wb * span, hi = min(seg, lo + span);
-    for (int i0 = lo; i0 < hi; i0 += 256) {
-        if (threadIdx.x == 0) nkept = 0;
-        __syncthreads();
-        const int i = i0 + (int)threadIdx.x;
-        if (i < hi) {
-            const uint32_t task = tasks[x * seg + i];
-            if (task != NOLSM_TASK_NONE && !cd.ctl[task_slot(task)].done) kept[atomicAdd(&nkept, 1)] = task;
-        }
-        __syncthreads();
-        const int nk = nkept;
-        for (int k = 0; k < nk; ++k) {
-            run(kept[k]);
-            __syncthreads();   // its LDS is free again
-        }
-        __syncthreads();
-    }
+// the slots that a scanning launch still has to work on
+__device__ __forceinline__ auto iterating(const ChunkDev &cd) {
+    return [&cd](int s) { return !cd.ctl[s].done; };
 }
 
 // The iterations from `it0` on of a small chunk as one launch: its workgroups
-// scan their tasks as above and work on every submatrix that still iterates
+// scan their tasks (scan_tasks) and work on every submatrix that still iterates
 // until it is done. What bounds the late launches of a small chunk is their
 // number: 48 (FP16) or 60 (FP64) a chunk, 2.5 to 4.5 us each, when all is
 // converged (64 submatrices of about 350 rows: 834 -> 583 us of iteration in
@@ -414,12 +389,12 @@ __device__ __forceinline__ void rest_of(SubCtl *ctl, int nt, int bstep, int it0,
 }
 template <typename T, int NC>
 __global__ __launch_bounds__(256, 2) void k_ns64_tail(ChunkDev cd, char *ws, NsArgs na, int it, int mode) {
-    scan_tasks(cd, cd.t_ns, cd.n_ns, [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
+    scan_tasks(cd.t_ns, cd.n_ns, iterating(cd), [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
 }
 
 template <typename T, int NC>
 __global__ __launch_bounds__(256, 2) void k_ns64_rest(ChunkDev cd, char *ws, NsArgs na, int it0) {
-    scan_tasks(cd, cd.t_ns, cd.n_ns, [&](uint32_t task) {
+    scan_tasks(cd.t_ns, cd.n_ns, iterating(cd), [&](uint32_t task) {
         const int s = task_slot(task);
         rest_of<false>(cd.ctl + s, cd.meta[s].np / 64, NC / 2, it0, na.max_iter, [&](int a, int b, int it, int mode) {
             ns64_tile<T, NC>(cd, NOLSM_TASK(s, a, b), ws, na, it, mode);
@@ -611,13 +586,13 @@ __global__ __launch_bounds__(256, 3) void k_ns_lp_pq(ChunkDev cd, const uint32_t
 template <typename T, int BM, bool SYM>
 __global__ __launch_bounds__(256, 2) void k_ns_lp_tail(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws,
                                                     NsArgs na, int it, int mode) {
-    scan_tasks(cd, tasks, ntask, [&](uint32_t task) { ns_tile<T, BM, SYM>(cd, task, ws, na, it, mode); });
+    scan_tasks(tasks, ntask, iterating(cd), [&](uint32_t task) { ns_tile<T, BM, SYM>(cd, task, ws, na, it, mode); });
 }
 
 template <typename T, int BM, bool SYM>
 __global__ __launch_bounds__(256, 2) void k_ns_lp_rest(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws,
                                                     NsArgs na, int it0) {
-    scan_tasks(cd, tasks, ntask, [&](uint32_t task) {
+    scan_tasks(tasks, ntask, iterating(cd), [&](uint32_t task) {
         const int s = task_slot(task);
         rest_of<SYM>(cd.ctl + s, (cd.meta[s].np + BM - 1) / BM, 1, it0, na.max_iter,
                      [&](int a, int b, int it, int mode) {
@@ -642,12 +617,6 @@ __global__ __launch_bounds__(256, 2) void k_ns_lp_rest(ChunkDev cd, const uint32
 #define NS_REST_IT 16
 #define NS64_REST_IT 22
 static bool rest_chunk(const NsArgs &na, int ntask) { return ntask <= 8 * na.pgrid; }
-// grid of both: four scanning workgroups per CU (2 x pgrid), at most one per task
-static int scan_grid(const NsArgs &na, int ntask) {
-    const int g = (2 * na.pgrid < ntask ? 2 * na.pgrid : ntask) / 8 * 8;
-    return g < 8 ? 8 : g;
-}
-
 // queue counters of one launch: [iteration][half][tile class][XCD]
 static int *launch_queue(const ChunkDev &cd, int it, int mode, int cls) {
     return cd.queues + (((size_t)it * 2 + (mode - 1)) * 2 + cls) * 8;
@@ -668,10 +637,10 @@ static void launch_lp(const ChunkDev &cd, const uint32_t *tasks, int ntask, char
     else if (it < NS_TAIL_IT)
         hipLaunchKernelGGL((k_ns_lp<T, BM, SYM>), dim3(ntask), dim3(256), 0, st, cd, tasks, ws, na, it, mode);
     else if (it < NS_REST_IT || !rest_chunk(na, ntask))
-        hipLaunchKernelGGL((k_ns_lp_tail<T, BM, SYM>), dim3(scan_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+        hipLaunchKernelGGL((k_ns_lp_tail<T, BM, SYM>), dim3(scan_grid(na.pgrid, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
                            na, it, mode);
     else if (it == NS_REST_IT && mode == 1)
-        hipLaunchKernelGGL((k_ns_lp_rest<T, BM, SYM>), dim3(scan_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+        hipLaunchKernelGGL((k_ns_lp_rest<T, BM, SYM>), dim3(scan_grid(na.pgrid, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
                            na, it);
 }
 template <typename T, bool SYM>
@@ -689,9 +658,9 @@ static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, in
     else if (it < NS64_TAIL_IT)
         hipLaunchKernelGGL((k_ns64<T, NC>), dim3(cd.n_ns), dim3(256), 0, st, cd, ws, na, it, mode);
     else if (it < NS64_REST_IT || !rest_chunk(na, cd.n_ns))
-        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
+        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na.pgrid, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
     else if (it == NS64_REST_IT && mode == 1)
-        hipLaunchKernelGGL((k_ns64_rest<T, NC>), dim3(scan_grid(na, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it);
+        hipLaunchKernelGGL((k_ns64_rest<T, NC>), dim3(scan_grid(na.pgrid, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it);
 }
 template <typename T>
 static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
