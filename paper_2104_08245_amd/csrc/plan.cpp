@@ -584,13 +584,13 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                 ch.max_own = std::max(ch.max_own, m.nown);
                 for (int32_t c = 0; c <= m.P; ++c) ch.t_subst.push_back(NOLSM_TASK(s, c, 0));
                 // X_0 tiles: the symmetric route converts the upper ones (each
-                // also writes its mirror)
+                // also writes its mirror where that is stored)
                 for (int32_t a = 0; a < m.P; ++a)
                     for (int32_t b = pl->sym ? a : 0; b < m.P; ++b) ch.t_conv.push_back(NOLSM_TASK(s, a, b));
                 // FP16/BF16 slots with 64-row tiles get their own list
                 std::vector<uint32_t> &tl =
                     (T == 64 && (pl->prec == NOLSM_FP16 || pl->prec == NOLSM_BF16)) ? ch.t_ns64 : ch.t_ns;
-                // symmetric route: upper tiles only, each mirrors itself
+                // symmetric route: upper tiles only
                 const bool sym = pl->sym != 0;
                 const int32_t bstep = ch.ns_wide ? 2 : 1;
                 for (int32_t a = 0; a < nt; ++a)
