@@ -9,6 +9,7 @@
 // later calls with the same buffers and options.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -132,6 +133,7 @@ static LaunchArgs make_args(const nolsm_plan *pl, const BatchArgs &b) {
     ga.own_J = (const int32_t *)(base + pl->o_own_J);
     ga.s_fp32 = o.inverse == NOLSM_INV_CHOLESKY_FP32;
     ga.Kval = b.dK;
+    ga.ws0 = b.ws;
     ga.Sval = b.dS;
     ga.bs = pl->bs;
     ga.poison_J = o.debug_poison_mol;
@@ -272,6 +274,77 @@ static int enqueue(nolsm_plan *pl, const BatchArgs &b, hipStream_t st, PhaseEven
     return NOLSM_OK;
 }
 
+// Graph schedule with a region per chunk: the chunks side by side on LANES
+// streams, the call's own and the library's, which fork from it and join back
+// into it (so a capture holds them all, and what the caller does next on its
+// stream waits for all of them). A chunk goes to the lane with the least work.
+// A chunk is a chain of launches that each end in a partly empty wave, and a
+// small one leaves most of the GPU idle: beside each other a slab of 2,048
+// molecules (5 chunks) takes 149.3 instead of 161.3 ms, a bisection on 216
+// molecules 4.1 instead of 6.0 ms, 64 molecules in FP64 on the default stream
+// 1.53 instead of 2.10 ms. (Two lanes: 2,000 molecules combined 35.5 instead of
+// 34.5 ms; four: the bisection 4.4 instead of 4.1.)
+#define LANES 3
+// Not for small calls on a stream of the caller's: graphs that fork do not run
+// beside each other, and where calls from several streams fill the GPU
+// together that costs more than it gives (four streams: 64 molecules FP64 981
+// -> 1520 us a call, a slab of 400 FP64 3045 -> 3387). From about 5e9 padded
+// rows^3 on it no longer does (216 molecules of about 300 rows FP16 1741 -> 1473,
+// FP64 9429 -> 9497; a slab of 800 FP16 5668 -> 4781, FP64 44.9 -> 43.9 ms).
+// Calls on the default stream run in turn anyway.
+static bool side_by_side(const nolsm_plan *pl, const nolsm_solve_opts *o, hipStream_t st) {
+    if (!pl->side || o->sched != NOLSM_SCHED_GRAPH) return false;
+    double work = 0.0;
+    for (const HostChunk &ch : pl->chunks)
+        for (const SubMeta &m : ch.meta) work += (double)m.np * m.np * m.np;
+    return st == nullptr || work >= 4e9;
+}
+
+static int side_resources(nolsm_plan *pl, size_t nlane) {
+    while (pl->lanes.size() + 1 < nlane) {
+        hipStream_t s = nullptr;
+        hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e != hipSuccess) return hip_fail(e, "chunk stream");
+        pl->lanes.push_back(s);
+    }
+    while (pl->lane_events.size() < nlane) {
+        hipEvent_t ev = nullptr;
+        hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "chunk event");
+        pl->lane_events.push_back(ev);
+    }
+    return NOLSM_OK;
+}
+
+static int enqueue_side(nolsm_plan *pl, const BatchArgs &b, hipStream_t st) {
+    std::lock_guard<std::mutex> lock(pl->lane_mu);
+    const size_t nlane = std::min<size_t>(LANES, pl->chunks.size());
+    int rc = side_resources(pl, nlane);
+    if (rc != NOLSM_OK) return rc;
+    const LaunchArgs A = make_args(pl, b);
+    auto stream = [&](size_t l) { return l ? (hipStream_t)pl->lanes[l - 1] : st; };
+    auto ev = [&](size_t l) { return (hipEvent_t)pl->lane_events[l]; };   // 0: the fork, else lane l's end
+    hipError_t e = hipEventRecord(ev(0), st);
+    size_t forked = 1;
+    for (; e == hipSuccess && forked < nlane; ++forked)
+        if ((e = hipStreamWaitEvent(stream(forked), ev(0), 0)) != hipSuccess) break;
+    if (e != hipSuccess) rc = hip_fail(e, "chunk fork");
+    double load[LANES] = {};
+    for (const HostChunk &ch : pl->chunks) {
+        if (rc != NOLSM_OK) break;
+        const size_t l = std::min_element(load, load + nlane) - load;
+        for (const SubMeta &m : ch.meta) load[l] += (double)m.np * m.np * m.np;
+        rc = enqueue_setup(pl, b, A, ch, stream(l), nullptr);
+        if (rc == NOLSM_OK) rc = enqueue_solve(pl, b, A, ch, stream(l), nullptr);
+    }
+    // what was forked is joined, also after an error
+    for (size_t l = 1; l < forked; ++l) {
+        if ((e = hipEventRecord(ev(l), stream(l))) == hipSuccess) e = hipStreamWaitEvent(st, ev(l), 0);
+        if (e != hipSuccess && rc == NOLSM_OK) rc = hip_fail(e, "chunk join");
+    }
+    return rc;
+}
+
 // Pipeline schedule: the chunks alternate between two workspace regions.
 // The setups run in order on the library's stream s2 and the solves in
 // order on the call's stream st; solve(c) waits for setup(c), and setup(c)
@@ -361,18 +434,11 @@ static int check_batch(const nolsm_plan *pl, const double *dK_val, const double 
 }
 
 // mu lives in the workspace header (outside any captured graph), so a
-// captured batch serves every mu; the pipeline's second region has a header
-// of its own
-static int write_headers(const nolsm_plan *pl, char *ws, double mu, hipStream_t st) {
+// captured batch serves every mu; k_init_ctl copies it to the headers of the
+// other regions
+static int write_header(char *ws, double mu, hipStream_t st) {
     hipError_t e = launch_set_header(ws, mu, st);
-    if (e != hipSuccess) return hip_fail(e, "header launch");
-    for (const HostChunk &ch : pl->chunks)
-        if (ch.base) {
-            e = launch_set_header(ws + ch.base, mu, st);
-            if (e != hipSuccess) return hip_fail(e, "header launch");
-            break;
-        }
-    return NOLSM_OK;
+    return e == hipSuccess ? NOLSM_OK : hip_fail(e, "header launch");
 }
 
 extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
@@ -382,7 +448,8 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, (char *)d_ws, dDcols, dD_val, (void *)dstats};
-    if ((rc = write_headers(pl, (char *)d_ws, mu, st)) != NOLSM_OK) return rc;
+    if ((rc = write_header((char *)d_ws, mu, st)) != NOLSM_OK) return rc;
+    const bool side = side_by_side(pl, opts, st);
     if (opts->profile) {
         PhaseEvents pe;
         pe.st = st;
@@ -414,7 +481,9 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
             drop_graph(pl);
             hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_fail(e, "graph capture begin");
-            rc = opts->sched == NOLSM_SCHED_PIPELINE ? enqueue_pipe(pl, b, st) : enqueue(pl, b, st);
+            rc = opts->sched == NOLSM_SCHED_PIPELINE ? enqueue_pipe(pl, b, st)
+                 : side                              ? enqueue_side(pl, b, st)
+                                                     : enqueue(pl, b, st);
             hipGraph_t g = nullptr;
             e = hipStreamEndCapture(st, &g);
             if (rc != NOLSM_OK) {
@@ -436,7 +505,7 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
         if (e != hipSuccess) return hip_fail(e, "graph launch");
         rc = NOLSM_OK;
     } else {
-        rc = enqueue(pl, b, st);
+        rc = side ? enqueue_side(pl, b, st) : enqueue(pl, b, st);
         if (rc != NOLSM_OK) return rc;
     }
     if (opts->sync_errors) {
@@ -522,7 +591,7 @@ extern "C" int nolsm_sign_batch_noalloc(nolsm_plan *pl, const double *dK_val, co
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, ws, dDcols, dD_val, (void *)dstats};
-    if ((rc = write_headers(pl, ws, mu, st)) != NOLSM_OK) return rc;
+    if ((rc = write_header(ws, mu, st)) != NOLSM_OK) return rc;
     // every kernel initialises the workspace state it reads (control blocks,
     // queue counters, residual partials) within the call, so contents left by
     // an earlier call are never read
@@ -611,5 +680,7 @@ extern "C" void nolsm_plan_destroy(nolsm_plan *pl) {
     drop_graph(pl);
     for (void *ev : pl->events) (void)hipEventDestroy((hipEvent_t)ev);
     if (pl->aux_stream) (void)hipStreamDestroy((hipStream_t)pl->aux_stream);
+    for (void *ev : pl->lane_events) (void)hipEventDestroy((hipEvent_t)ev);
+    for (void *s : pl->lanes) (void)hipStreamDestroy((hipStream_t)s);
     delete pl;
 }

@@ -1677,7 +1677,9 @@ __global__ __launch_bounds__(256) void k_convert(ChunkDev cd, char *ws, int use_
 }
 
 // init of the per-slot control blocks and residual partials of a chunk
-__global__ void k_init_ctl(ChunkDev cd) {
+// ws0: start of the workspace, whose header the caller has set; a chunk in a
+// region of its own reads mu from that region's header
+__global__ void k_init_ctl(ChunkDev cd, char *ws, const char *ws0) {
     const int s = blockIdx.x;
     if (s >= cd.nsub) return;
     SubCtl *c = cd.ctl + s;
@@ -1689,13 +1691,14 @@ __global__ void k_init_ctl(ChunkDev cd) {
     for (int i = threadIdx.x; i < NOLSM_MAX_ITER_CAP; i += blockDim.x) c->rhist[i] = 0.0;
     if (s == 0)
         for (int i = threadIdx.x; i < cd.nqueue; i += blockDim.x) cd.queues[i] = 0;
+    if (s == 0 && threadIdx.x == 0 && ws != ws0) ((WsHeader *)ws)->mu = ((const WsHeader *)ws0)->mu;
 }
 
 // ----------------------------------------------------------------- launchers
 #define LAUNCH_CHECK() do { hipError_t e_ = hipGetLastError(); if (e_ != hipSuccess) return e_; } while (0)
 
 hipError_t launch_gather(const ChunkDev &cd, char *ws, const GatherArgs &ga, hipStream_t st) {
-    hipLaunchKernelGGL(k_init_ctl, dim3(cd.nsub), dim3(64), 0, st, cd);
+    hipLaunchKernelGGL(k_init_ctl, dim3(cd.nsub), dim3(64), 0, st, cd, ws, ga.ws0);
     LAUNCH_CHECK();
     const size_t lds = (size_t)cd.max_m * 3 * sizeof(int);
     hipLaunchKernelGGL(k_gather, dim3(cd.max_m, cd.nsub), dim3(256), lds, st, cd, ws, ga);

@@ -3,6 +3,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -20,7 +21,8 @@ struct HostChunk {
     size_t off_ictl = 0;      // workspace offset of the InvCtl array (0: none)
     size_t off_q = 0;         // workspace offset of the queue counters
     size_t base = 0;          // offset of the chunk's region in the workspace
-                              // (pipeline schedule: two regions in turn)
+                              // (pipeline schedule: two regions in turn; graph
+                              // schedule: one each where there is room)
     // metadata image offsets (bytes from d_meta)
     size_t o_meta = 0, o_subst = 0, o_conv = 0, o_ns = 0, o_ns64 = 0, o_rows = 0;
 };
@@ -61,6 +63,12 @@ struct nolsm_plan {
     // pipeline schedule: the library's second stream and its order events
     void *aux_stream = nullptr;
     std::vector<void *> events;
+    // graph schedule, chunks side by side (`side`: every chunk has a region of
+    // its own): streams beside the call's, and the events that fork and join
+    // them, held for one call's launches at a time
+    bool side = false;
+    std::vector<void *> lanes, lane_events;
+    std::mutex lane_mu;
     nolsm_profile prof = {};
 };
 
