@@ -285,19 +285,26 @@ static int enqueue(nolsm_plan *pl, const BatchArgs &b, hipStream_t st, PhaseEven
 // 1.53 instead of 2.10 ms. (Two lanes: 2,000 molecules combined 35.5 instead of
 // 34.5 ms; four: the bisection 4.4 instead of 4.1.)
 #define LANES 3
-// Not for small calls on a stream of the caller's: graphs that fork do not run
-// beside each other, and where calls from several streams fill the GPU
-// together that costs more than it gives (four streams: 64 molecules FP64 981
-// -> 1520 us a call, a slab of 400 FP64 3045 -> 3387). From about 5e9 padded
-// rows^3 on it no longer does (216 molecules of about 300 rows FP16 1741 -> 1473,
-// FP64 9429 -> 9497; a slab of 800 FP16 5668 -> 4781, FP64 44.9 -> 43.9 ms).
-// Calls on the default stream run in turn anyway.
-static bool side_by_side(const nolsm_plan *pl, const nolsm_solve_opts *o, hipStream_t st) {
+// On a stream of the caller's that is weighed against what calls from other
+// streams lose, since graphs that fork do not run beside each other: small
+// calls, which fill the GPU only together (four streams: 64 molecules FP64 981
+// -> 1520 us a call, a slab of 400 FP64 3045 -> 3387), and calls whose work is
+// nearly all in one chunk (1,000 molecules FP16 on A_J, 5% outside it, 43.5 ->
+// 46.6 ms) stay in turn; from 4e9 padded rows^3 on with an eighth of them outside
+// the largest chunk they gain (the slab above has 19%, the combined molecules
+// 52%; a slab of 800, 22%: 4.7 instead of 5.7 ms with four streams). A call
+// that is waited for (`waits`) and calls on the default stream run alone.
+static bool side_by_side(const nolsm_plan *pl, const nolsm_solve_opts *o, hipStream_t st, bool waits) {
     if (!pl->side || o->sched != NOLSM_SCHED_GRAPH) return false;
-    double work = 0.0;
-    for (const HostChunk &ch : pl->chunks)
-        for (const SubMeta &m : ch.meta) work += (double)m.np * m.np * m.np;
-    return st == nullptr || work >= 4e9;
+    if (st == nullptr || waits) return true;
+    double work = 0.0, most = 0.0;
+    for (const HostChunk &ch : pl->chunks) {
+        double w = 0.0;
+        for (const SubMeta &m : ch.meta) w += (double)m.np * m.np * m.np;
+        work += w;
+        most = std::max(most, w);
+    }
+    return work >= 4e9 && work - most >= work / 8;
 }
 
 static int side_resources(nolsm_plan *pl, size_t nlane) {
@@ -441,15 +448,16 @@ static int write_header(char *ws, double mu, hipStream_t st) {
     return e == hipSuccess ? NOLSM_OK : hip_fail(e, "header launch");
 }
 
-extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
-                                const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols,
-                                double *dD_val, nolsm_mol_stats *dstats, void *stream) {
+// `waits`: the caller waits for the solve before it enqueues more
+static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
+                      const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols, double *dD_val,
+                      nolsm_mol_stats *dstats, void *stream, bool waits) {
     int rc = check_batch(pl, dK_val, dS_val, opts, d_ws, ws_bytes, dDcols, dstats);
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, (char *)d_ws, dDcols, dD_val, (void *)dstats};
     if ((rc = write_header((char *)d_ws, mu, st)) != NOLSM_OK) return rc;
-    const bool side = side_by_side(pl, opts, st);
+    const bool side = side_by_side(pl, opts, st, waits || opts->sync_errors);
     if (opts->profile) {
         PhaseEvents pe;
         pe.st = st;
@@ -475,7 +483,7 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
     } else if ((opts->sched == NOLSM_SCHED_GRAPH || opts->sched == NOLSM_SCHED_PERSISTENT ||
                 opts->sched == NOLSM_SCHED_PIPELINE) && st != nullptr) {
         const void *key[6] = {dK_val, dS_val, d_ws, dDcols, dD_val, dstats};
-        bool hit = pl->graph_exec && pl->g_stream == stream && same_opts(pl->g_opts, *opts);
+        bool hit = pl->graph_exec && pl->g_stream == stream && pl->g_side == side && same_opts(pl->g_opts, *opts);
         for (int i = 0; i < 6 && hit; ++i) hit = pl->g_key[i] == key[i];
         if (!hit) {
             drop_graph(pl);
@@ -500,6 +508,7 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
             pl->g_mu = mu;
             pl->g_opts = *opts;
             pl->g_stream = stream;
+            pl->g_side = side;
         }
         hipError_t e = hipGraphLaunch((hipGraphExec_t)pl->graph_exec, st);
         if (e != hipSuccess) return hip_fail(e, "graph launch");
@@ -522,6 +531,12 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
         }
     }
     return NOLSM_OK;
+}
+
+extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
+                                const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols,
+                                double *dD_val, nolsm_mol_stats *dstats, void *stream) {
+    return sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream, false);
 }
 
 // ------------------------------------------------- allocation-free variant
@@ -632,7 +647,7 @@ extern "C" int nolsm_mu_bisect(nolsm_plan *pl, const double *dK_val, const doubl
     int32_t step = 0;
     for (step = 1; step <= max_steps; ++step) {
         mu = 0.5 * (lo + hi);
-        int rc = nolsm_sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream);
+        int rc = sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream, true);
         if (rc != NOLSM_OK) return rc;
         double sums[3];
         rc = nolsm_trace_sums(pl, dstats, d_ws, sums, stream);

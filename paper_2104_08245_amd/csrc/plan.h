@@ -60,6 +60,7 @@ struct nolsm_plan {
     double g_mu = 0.0;
     nolsm_solve_opts g_opts;
     void *g_stream = nullptr;
+    bool g_side = false;      // captured with the chunks side by side
     // pipeline schedule: the library's second stream and its order events
     void *aux_stream = nullptr;
     std::vector<void *> events;

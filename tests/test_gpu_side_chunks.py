@@ -55,8 +55,10 @@ def test_chunks_side_by_side_are_the_same(torch, systems, name, prec, route):
     want0, full = in_turn(None)
     one, two = torch.cuda.Stream(), torch.cuda.Stream()
     other = Solver(s, prec=prec, **route)
-    for ws_bytes, stream in ((None, one), (None, None), (full + (1 << 20), one), (full // 2, one)):
-        sv = Solver(s, prec=prec, ws_bytes=ws_bytes, **route)
+    # side by side: on the default stream, and in a graph where the call is waited for
+    for ws_bytes, stream, sync in ((None, one, 0), (None, one, 1), (None, None, 0), (full + (1 << 20), one, 1),
+                                   (full // 2, one, 1)):
+        sv = Solver(s, prec=prec, ws_bytes=ws_bytes, sync_errors=sync, **route)
         want = in_turn(ws_bytes)[0]   # the same chunks
         for k, mu in enumerate(mus):
             print("[gpu]", name, prec, ws_bytes, stream is None, mu, flush=True)
