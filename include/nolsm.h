@@ -370,8 +370,10 @@ int nolsm_sign_batch(nolsm_plan *plan, const double *dK_val, const double *dS_va
  * caller. It calls no hipMalloc / hipFree and no allocating routine; the
  * first call on a device looks up the array's address there.
  * Every call on one GPU shares that GPU's array, which keeps the last call's
- * contents (each call initialises what it reads): calls that overlap on one
- * GPU (several streams or threads) race and must be serialised by the caller.
+ * contents (each call initialises what it reads). Calls from several streams
+ * or threads run one after the other: each waits, on its stream, for the end of
+ * the one before. Only captured calls take no part in that: their replays
+ * must be serialised by the caller with each other and with other calls.
  * Errors: as nolsm_sign_batch; E_WORKSPACE when the plan's workspace exceeds
  * the array; E_ARG for the pipeline schedule, profile or sync_errors (each
  * would create library streams, events or host buffers); E_STATE when the

@@ -569,6 +569,30 @@ static int scratch_address(int dev, char **out) {
     return NOLSM_OK;
 }
 
+// Order of the calls that share a device's array: a call waits on its stream
+// for the end of the one before, whichever stream that was on. (Calls from
+// several streams used to be apart only because the host took longer to launch
+// one than the GPU to run it.) One call's launches at a time; a call under the
+// caller's capture takes no part, its replays are the caller's to order.
+struct ScratchOrder {
+    std::mutex mu;
+    hipEvent_t end = nullptr;
+    bool any = false;
+};
+static ScratchOrder scratch_order[NOLSM_NOALLOC_MAX_DEVICES];
+
+static int scratch_begin(ScratchOrder &o, hipStream_t st, bool *ordered) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t e = st ? hipStreamIsCapturing(st, &cs) : hipSuccess;
+    if (e != hipSuccess) return hip_fail(e, "capture status");
+    *ordered = cs == hipStreamCaptureStatusNone;
+    if (!*ordered) return NOLSM_OK;
+    if (!o.end && (e = hipEventCreateWithFlags(&o.end, hipEventDisableTiming)) != hipSuccess)
+        return hip_fail(e, "scratch order event");
+    if (o.any && (e = hipStreamWaitEvent(st, o.end, 0)) != hipSuccess) return hip_fail(e, "scratch order wait");
+    return NOLSM_OK;
+}
+
 extern "C" int nolsm_sign_batch_noalloc(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
                                         const nolsm_solve_opts *opts, double *dDcols, double *dD_val,
                                         nolsm_mol_stats *dstats, void *stream) {
@@ -606,11 +630,21 @@ extern "C" int nolsm_sign_batch_noalloc(nolsm_plan *pl, const double *dK_val, co
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, ws, dDcols, dD_val, (void *)dstats};
-    if ((rc = write_header(ws, mu, st)) != NOLSM_OK) return rc;
+    ScratchOrder &order = scratch_order[dev];
+    std::lock_guard<std::mutex> lock(order.mu);
+    bool ordered = false;
+    if ((rc = scratch_begin(order, st, &ordered)) != NOLSM_OK) return rc;
     // every kernel initialises the workspace state it reads (control blocks,
     // queue counters, residual partials) within the call, so contents left by
     // an earlier call are never read
-    return enqueue(pl, b, st);
+    rc = write_header(ws, mu, st);
+    if (rc == NOLSM_OK) rc = enqueue(pl, b, st);
+    if (ordered) {   // also after an error: part of the call may be on its way
+        e = hipEventRecord(order.end, st);
+        if (e == hipSuccess) order.any = true;
+        else if (rc == NOLSM_OK) rc = hip_fail(e, "scratch order record");
+    }
+    return rc;
 }
 
 extern "C" int nolsm_trace_sums(const nolsm_plan *pl, const nolsm_mol_stats *dstats, void *d_ws,
