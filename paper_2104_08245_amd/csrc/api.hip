@@ -280,7 +280,7 @@ static int enqueue(nolsm_plan *pl, const BatchArgs &b, hipStream_t st, PhaseEven
 // stream waits for all of them). A chunk goes to the lane with the least work.
 // A chunk is a chain of launches that each end in a partly empty wave, and a
 // small one leaves most of the GPU idle: beside each other a slab of 2,048
-// molecules (5 chunks) takes 149.3 instead of 161.3 ms, a bisection on 216
+// molecules (6 chunks) takes 149.3 instead of 161.3 ms, a bisection on 216
 // molecules 4.1 instead of 6.0 ms, 64 molecules in FP64 on the default stream
 // 1.53 instead of 2.10 ms. (Two lanes: 2,000 molecules combined 35.5 instead of
 // 34.5 ms; four: the bisection 4.4 instead of 4.1.)
