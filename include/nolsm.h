@@ -352,7 +352,10 @@ int nolsm_plan_bind(nolsm_plan *plan, void *d_meta, size_t meta_bytes, void *str
  * the caller reads after synchronizing; with opts->sync_errors the call
  * synchronizes and returns E_NOT_SPD / E_NOCONV if any molecule failed.
  * Errors: E_ARG, E_STATE (plan not configured/bound for opts->prec,
- * opts->sched or a larger workspace), E_WORKSPACE, E_HIP. */
+ * opts->sched or a larger workspace; the schedules that run the chunks in turn
+ * serve each other's plans, but NOLSM_SCHED_PIPELINE refuses a plan of several
+ * chunks that was configured for another one and whose chunks share their
+ * workspace), E_WORKSPACE, E_HIP. */
 int nolsm_sign_batch(nolsm_plan *plan, const double *dK_val, const double *dS_val,
                      double mu, const nolsm_solve_opts *opts, void *d_ws,
                      size_t ws_bytes, double *dDcols, double *dD_val,

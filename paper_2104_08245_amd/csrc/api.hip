@@ -406,10 +406,17 @@ static bool same_opts(const nolsm_solve_opts &a, const nolsm_solve_opts &b) {
 // argument checks shared by the batch entry points
 static int check_batch(const nolsm_plan *pl, const double *dK_val, const double *dS_val,
                        const nolsm_solve_opts *opts, const void *d_ws, size_t ws_bytes, const double *dDcols,
-                       const nolsm_mol_stats *dstats) {
+                       const nolsm_mol_stats *dstats, const void *stream) {
     if (!pl || !dK_val || !dS_val || !opts || !d_ws || !dDcols || !dstats) {
         nolsm_set_last_error("sign_batch: null argument");
         return NOLSM_E_ARG;
+    }
+    // the pipeline prepares a chunk beside the solve of the one before, which
+    // configure keeps in other bytes only where it knows of it (on the null
+    // stream and with `profile` the chunks run in turn, in any layout)
+    if (opts->sched == NOLSM_SCHED_PIPELINE && stream && !opts->profile && pl->configured && !pl->apart) {
+        nolsm_set_last_error("sign_batch: plan not configured for the pipeline schedule");
+        return NOLSM_E_STATE;
     }
     if (!pl->bound) { nolsm_set_last_error("sign_batch: plan not bound"); return NOLSM_E_STATE; }
     if (opts->prec != pl->prec || opts->max_iter != pl->max_iter || opts->inverse != pl->inverse ||
@@ -452,7 +459,7 @@ static int write_header(char *ws, double mu, hipStream_t st) {
 static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
                       const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols, double *dD_val,
                       nolsm_mol_stats *dstats, void *stream, bool waits) {
-    int rc = check_batch(pl, dK_val, dS_val, opts, d_ws, ws_bytes, dDcols, dstats);
+    int rc = check_batch(pl, dK_val, dS_val, opts, d_ws, ws_bytes, dDcols, dstats, stream);
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, (char *)d_ws, dDcols, dD_val, (void *)dstats};
@@ -626,7 +633,7 @@ extern "C" int nolsm_sign_batch_noalloc(nolsm_plan *pl, const double *dK_val, co
     char *ws = nullptr;
     int rc = scratch_address(dev, &ws);
     if (rc != NOLSM_OK) return rc;
-    rc = check_batch(pl, dK_val, dS_val, opts, ws, (size_t)NOLSM_NOALLOC_WS_BYTES, dDcols, dstats);
+    rc = check_batch(pl, dK_val, dS_val, opts, ws, (size_t)NOLSM_NOALLOC_WS_BYTES, dDcols, dstats, stream);
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, ws, dDcols, dD_val, (void *)dstats};

@@ -625,6 +625,7 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                 at += align256(ch.ws_used);
             }
         }
+        pl->apart = pipe || pl->side || pl->chunks.size() <= 1;
         // metadata image
         pl->image.clear();
         pl->o_Krp = put(pl->image, pl->Krp.data(), pl->Krp.size());

@@ -48,6 +48,7 @@ struct nolsm_plan {
     int32_t inverse = 0, inv_max_iter = 0, sym = 0;
     size_t ws_bytes = 0, ws_min = 0, ws_full = 0;
     std::vector<HostChunk> chunks;
+    bool apart = false;                   // chunks that follow each other share no workspace bytes
     std::vector<char> image;              // metadata image uploaded by bind
     size_t o_Krp = 0, o_Kci = 0, o_Srp = 0, o_Sci = 0, o_sub_ptr = 0, o_sub_blk = 0,
            o_self = 0, o_scatter = 0, o_grp_blk = 0, o_own_J = 0, o_own_pos = 0, o_rowpos = 0;
