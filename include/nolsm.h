@@ -363,25 +363,30 @@ int nolsm_sign_batch(nolsm_plan *plan, const double *dK_val, const double *dS_va
 
 /* Allocation-free variant of nolsm_sign_batch, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): the workspace is a device array of the
- * library, NOLSM_NOALLOC_WS_BYTES per GPU, held by every GPU the library runs
- * on until the process ends. Same arguments and results as nolsm_sign_batch
- * without d_ws / ws_bytes; the plan must be configured with
- * ws_bytes <= NOLSM_NOALLOC_WS_BYTES (more chunks for a large batch) and bound
- * on the current device. The kernels are launched directly on `stream` (never
- * a graph of the library's), so the call may itself be captured by the
- * caller. It calls no hipMalloc / hipFree and no allocating routine; the
- * first call on a device looks up the array's address there.
- * Every call on one GPU shares that GPU's array, which keeps the last call's
- * contents (each call initialises what it reads). Calls from several streams
- * or threads run one after the other: each waits, on its stream, for the end of
- * the one before. Only captured calls take no part in that: their replays
- * must be serialised by the caller with each other and with other calls.
+ * harnesses that forbid hipMalloc): the workspace is one of
+ * NOLSM_NOALLOC_CALLS device arrays of the library, NOLSM_NOALLOC_WS_BYTES
+ * each, held by every GPU on which a call has used it until the process ends.
+ * Same arguments and results as nolsm_sign_batch without d_ws / ws_bytes; the
+ * plan must be configured with ws_bytes <= NOLSM_NOALLOC_WS_BYTES (more chunks
+ * for a large batch) and bound on the current device. The kernels are launched
+ * directly on `stream` (never a graph of the library's), so the call may
+ * itself be captured by the caller. It calls no hipMalloc / hipFree and no
+ * allocating routine and creates no HIP object (nolsm_plan_bind has the events
+ * that order the calls); the first call on a device that uses an array looks
+ * up its address there, which has the runtime load it.
+ * A call has its array to itself until its work ends, and finds there what an
+ * earlier call left (each call initialises what it reads). Calls from up to
+ * NOLSM_NOALLOC_CALLS streams, or threads, run side by side; a call from one
+ * more waits, on its stream, for the end of the call whose array it takes.
+ * Only captured calls take no part in that: they use the first array, and
+ * their replays must be serialised by the caller with each other and with
+ * other calls.
  * Errors: as nolsm_sign_batch; E_WORKSPACE when the plan's workspace exceeds
- * the array; E_ARG for the pipeline schedule, profile or sync_errors (each
+ * an array; E_ARG for the pipeline schedule, profile or sync_errors (each
  * would create library streams, events or host buffers); E_STATE when the
  * current device is not the plan's. */
 #define NOLSM_NOALLOC_WS_BYTES ((size_t)64 << 20)
+#define NOLSM_NOALLOC_CALLS 3
 int nolsm_sign_batch_noalloc(nolsm_plan *plan, const double *dK_val, const double *dS_val,
                              double mu, const nolsm_solve_opts *opts, double *dDcols,
                              double *dD_val, nolsm_mol_stats *dstats, void *stream);

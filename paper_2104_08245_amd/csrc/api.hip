@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -18,6 +19,7 @@
 
 #include "kernels.h"
 #include "plan.h"
+#include "scratch_part.h"
 
 static int hip_fail(hipError_t e, const char *where) {
     nolsm_set_last_error(std::string(where) + ": " + hipGetErrorString(e));
@@ -29,6 +31,74 @@ static void drop_graph(nolsm_plan *pl) {
         (void)hipGraphExecDestroy((hipGraphExec_t)pl->graph_exec);
         pl->graph_exec = nullptr;
     }
+}
+
+// The workspaces of nolsm_sign_batch_noalloc: NOLSM_NOALLOC_CALLS device
+// arrays of the library (scratch_part.h), on each GPU that it is called on.
+//
+// A call takes the array that its stream had last, or else the one that was
+// taken longest ago, and its stream waits for the end of the call that had it.
+// So calls of one stream stay in one array, and up to NOLSM_NOALLOC_CALLS
+// streams run side by side: a small solve leaves most of the GPU idle (calls on
+// three streams in turn, 64 molecules in FP64 1225 us a call, 25 in FP16 249;
+// 2672 and 792 with one array, where each waited for the one before). An array
+// belongs to one call's launches at a time. Calls under a caller's capture,
+// whose replays the library does not see, use the first and take no part in
+// the order.
+#define NOLSM_NOALLOC_MAX_DEVICES 64
+struct ScratchPart {
+    char *base = nullptr;
+    hipEvent_t end = nullptr;       // of the last call that had the array
+    hipStream_t stream = nullptr;   // and its stream
+    uint64_t turn = 0;
+    bool used = false, launching = false;
+};
+struct ScratchPool {
+    std::mutex mu;
+    std::condition_variable cv;
+    uint64_t turn = 0;
+    ScratchPart part[NOLSM_NOALLOC_CALLS];
+};
+static ScratchPool scratch_pools[NOLSM_NOALLOC_MAX_DEVICES];
+
+// the events, by bind, so that the calls create nothing
+static int scratch_events(int dev) {
+    ScratchPool &pool = scratch_pools[dev];
+    std::lock_guard<std::mutex> lock(pool.mu);
+    for (ScratchPart &q : pool.part) {
+        const hipError_t e = q.end ? hipSuccess : hipEventCreateWithFlags(&q.end, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "scratch order event");
+    }
+    return NOLSM_OK;
+}
+
+// address of array `part` on device `dev`, looked up once per device with that
+// device current (pool.mu held); the look-up is what loads the array
+static int scratch_address(int dev, int part, char **out) {
+    ScratchPart &q = scratch_pools[dev].part[part];
+    if (!q.base) {
+        void *p = nullptr;
+        hipError_t e = part == 0   ? scratch_symbol_0(&p)
+                       : part == 1 ? scratch_symbol_1(&p)
+                                   : scratch_symbol_2(&p);
+        if (e != hipSuccess) return hip_fail(e, "scratch symbol address");
+        if (!p || ((uintptr_t)p & 255)) {
+            nolsm_set_last_error("sign_batch_noalloc: scratch address not 256-byte aligned");
+            return NOLSM_E_HIP;
+        }
+        q.base = (char *)p;
+    }
+    *out = q.base;
+    return NOLSM_OK;
+}
+
+static void scratch_give(ScratchPool &pool, int part, bool recorded) {
+    {
+        std::lock_guard<std::mutex> lock(pool.mu);
+        if (recorded) pool.part[part].used = true;
+        pool.part[part].launching = false;
+    }
+    pool.cv.notify_all();
 }
 
 extern "C" int nolsm_plan_bind(nolsm_plan *pl, void *d_meta, size_t bytes, void *stream) {
@@ -43,10 +113,14 @@ extern "C" int nolsm_plan_bind(nolsm_plan *pl, void *d_meta, size_t bytes, void 
     if (e != hipSuccess) return hip_fail(e, "metadata upload");
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e, "metadata upload sync");
+    (void)hipGetDevice(&pl->device);
+    if (pl->device >= 0 && pl->device < NOLSM_NOALLOC_MAX_DEVICES) {
+        const int rc = scratch_events(pl->device);
+        if (rc != NOLSM_OK) return rc;
+    }
     drop_graph(pl);
     pl->d_meta = d_meta;
     pl->bound = true;
-    (void)hipGetDevice(&pl->device);
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pl->device) != hipSuccess || cus < 1)
         cus = 256;
@@ -547,56 +621,38 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
 }
 
 // ------------------------------------------------- allocation-free variant
-// The workspace of nolsm_sign_batch_noalloc: a device array of the library.
-// Every GPU the library runs on holds its own copy, at its own address, from
-// the load of the library's code until the process ends. In host code the
-// name is a stand-in, not a device address: kernels get the address that
-// hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) char scratch[NOLSM_NOALLOC_WS_BYTES];
-
-#define NOLSM_NOALLOC_MAX_DEVICES 64
-static std::mutex scratch_mu;
-static char *scratch_ptr[NOLSM_NOALLOC_MAX_DEVICES];
-
-// device address of `scratch` on device `dev`, looked up once per device with
-// that device current
-static int scratch_address(int dev, char **out) {
-    std::lock_guard<std::mutex> lock(scratch_mu);
-    if (!scratch_ptr[dev]) {
-        void *p = nullptr;
-        hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess) return hip_fail(e, "scratch symbol address");
-        if (!p || ((uintptr_t)p & 255)) {
-            nolsm_set_last_error("sign_batch_noalloc: scratch address not 256-byte aligned");
-            return NOLSM_E_HIP;
-        }
-        scratch_ptr[dev] = (char *)p;
-    }
-    *out = scratch_ptr[dev];
-    return NOLSM_OK;
-}
-
-// Order of the calls that share a device's array: a call waits on its stream
-// for the end of the one before, whichever stream that was on. (Calls from
-// several streams used to be apart only because the host took longer to launch
-// one than the GPU to run it.) One call's launches at a time; a call under the
-// caller's capture takes no part, its replays are the caller's to order.
-struct ScratchOrder {
-    std::mutex mu;
-    hipEvent_t end = nullptr;
-    bool any = false;
-};
-static ScratchOrder scratch_order[NOLSM_NOALLOC_MAX_DEVICES];
-
-static int scratch_begin(ScratchOrder &o, hipStream_t st, bool *ordered) {
+// the array of a call on `st`, which then waits for the last call that had it;
+// part -1: a call under capture
+static int scratch_take(int dev, hipStream_t st, int *part, char **ws) {
+    ScratchPool &pool = scratch_pools[dev];
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     hipError_t e = st ? hipStreamIsCapturing(st, &cs) : hipSuccess;
     if (e != hipSuccess) return hip_fail(e, "capture status");
-    *ordered = cs == hipStreamCaptureStatusNone;
-    if (!*ordered) return NOLSM_OK;
-    if (!o.end && (e = hipEventCreateWithFlags(&o.end, hipEventDisableTiming)) != hipSuccess)
-        return hip_fail(e, "scratch order event");
-    if (o.any && (e = hipStreamWaitEvent(st, o.end, 0)) != hipSuccess) return hip_fail(e, "scratch order wait");
+    *part = -1;
+    std::unique_lock<std::mutex> lock(pool.mu);
+    if (cs != hipStreamCaptureStatusNone) return scratch_address(dev, 0, ws);
+    int best = -1;
+    while (best < 0) {
+        for (int p = 0; p < NOLSM_NOALLOC_CALLS; ++p) {
+            const ScratchPart &q = pool.part[p];
+            if (q.launching) continue;
+            if (q.used && q.stream == st) {
+                best = p;
+                break;
+            }
+            if (best < 0 || q.turn < pool.part[best].turn) best = p;
+        }
+        if (best < 0) pool.cv.wait(lock);
+    }
+    const int rc = scratch_address(dev, best, ws);
+    if (rc != NOLSM_OK) return rc;
+    ScratchPart &q = pool.part[best];
+    // also where the stream is the same: a handle may stand for a new stream
+    if (q.used && (e = hipStreamWaitEvent(st, q.end, 0)) != hipSuccess) return hip_fail(e, "scratch order wait");
+    q.launching = true;
+    q.stream = st;
+    q.turn = ++pool.turn;
+    *part = best;
     return NOLSM_OK;
 }
 
@@ -631,25 +687,27 @@ extern "C" int nolsm_sign_batch_noalloc(nolsm_plan *pl, const double *dK_val, co
         return NOLSM_E_STATE;
     }
     char *ws = nullptr;
-    int rc = scratch_address(dev, &ws);
-    if (rc != NOLSM_OK) return rc;
-    rc = check_batch(pl, dK_val, dS_val, opts, ws, (size_t)NOLSM_NOALLOC_WS_BYTES, dDcols, dstats, stream);
+    {
+        std::lock_guard<std::mutex> lock(scratch_pools[dev].mu);
+        const int rc = scratch_address(dev, 0, &ws);
+        if (rc != NOLSM_OK) return rc;
+    }
+    int rc = check_batch(pl, dK_val, dS_val, opts, ws, (size_t)NOLSM_NOALLOC_WS_BYTES, dDcols, dstats, stream);
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
+    int part = -1;
+    if ((rc = scratch_take(dev, st, &part, &ws)) != NOLSM_OK) return rc;
     BatchArgs b{dK_val, dS_val, mu, opts, ws, dDcols, dD_val, (void *)dstats};
-    ScratchOrder &order = scratch_order[dev];
-    std::lock_guard<std::mutex> lock(order.mu);
-    bool ordered = false;
-    if ((rc = scratch_begin(order, st, &ordered)) != NOLSM_OK) return rc;
     // every kernel initialises the workspace state it reads (control blocks,
     // queue counters, residual partials) within the call, so contents left by
     // an earlier call are never read
     rc = write_header(ws, mu, st);
     if (rc == NOLSM_OK) rc = enqueue(pl, b, st);
-    if (ordered) {   // also after an error: part of the call may be on its way
-        e = hipEventRecord(order.end, st);
-        if (e == hipSuccess) order.any = true;
-        else if (rc == NOLSM_OK) rc = hip_fail(e, "scratch order record");
+    if (part >= 0) {   // also after an error: part of the call may be on its way
+        ScratchPool &pool = scratch_pools[dev];
+        e = hipEventRecord(pool.part[part].end, st);
+        if (e != hipSuccess && rc == NOLSM_OK) rc = hip_fail(e, "scratch order record");
+        scratch_give(pool, part, e == hipSuccess);
     }
     return rc;
 }

@@ -1,0 +1,3 @@
+#include "scratch_part.h"
+
+SCRATCH_PART(0)
