@@ -391,8 +391,8 @@ static int side_resources(nolsm_plan *pl, size_t nlane) {
     return NOLSM_OK;
 }
 
-// (with pl->call_mu held)
 static int enqueue_side(nolsm_plan *pl, const BatchArgs &b, hipStream_t st) {
+    std::lock_guard<std::mutex> lock(pl->lane_mu);
     const size_t nlane = std::min<size_t>(LANES, pl->chunks.size());
     int rc = side_resources(pl, nlane);
     if (rc != NOLSM_OK) return rc;
@@ -557,7 +557,6 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
         pl->prof = p;
     } else if ((opts->sched == NOLSM_SCHED_GRAPH || opts->sched == NOLSM_SCHED_PERSISTENT ||
                 opts->sched == NOLSM_SCHED_PIPELINE) && st != nullptr) {
-        std::lock_guard<std::mutex> lock(pl->call_mu);
         const void *key[6] = {dK_val, dS_val, d_ws, dDcols, dD_val, dstats};
         GraphSlot &slot = pl->graphs[side];
         bool hit = slot.exec && slot.stream == stream && same_opts(slot.opts, *opts);
@@ -588,11 +587,9 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
         hipError_t e = hipGraphLaunch((hipGraphExec_t)slot.exec, st);
         if (e != hipSuccess) return hip_fail(e, "graph launch");
         rc = NOLSM_OK;
-    } else if (side) {
-        std::lock_guard<std::mutex> lock(pl->call_mu);
-        if ((rc = enqueue_side(pl, b, st)) != NOLSM_OK) return rc;
     } else {
-        if ((rc = enqueue(pl, b, st)) != NOLSM_OK) return rc;
+        rc = side ? enqueue_side(pl, b, st) : enqueue(pl, b, st);
+        if (rc != NOLSM_OK) return rc;
     }
     if (opts->sync_errors) {
         hipError_t e = hipStreamSynchronize(st);

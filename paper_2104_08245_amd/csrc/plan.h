@@ -71,13 +71,11 @@ struct nolsm_plan {
     std::vector<void *> events;
     // graph schedule, chunks side by side (`side`: every chunk has a region of
     // its own): streams beside the call's, and the events that fork and join
-    // them
+    // them, held for one call's launches at a time
     bool side = false;
     double work = 0.0, work_most = 0.0;   // padded rows^3 of all chunks and of the largest
     std::vector<void *> lanes, lane_events;
-    // held by a call while it uses the graphs, or the streams and events above:
-    // to the end of a capture, until which its streams take no other work
-    std::mutex call_mu;
+    std::mutex lane_mu;
     nolsm_profile prof = {};
 };
 
