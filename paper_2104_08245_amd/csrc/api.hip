@@ -372,7 +372,14 @@ static int enqueue(nolsm_plan *pl, const BatchArgs &b, hipStream_t st, PhaseEven
 static bool side_by_side(const nolsm_plan *pl, const nolsm_solve_opts *o, hipStream_t st, bool waits) {
     if (!pl->side || o->sched != NOLSM_SCHED_GRAPH) return false;
     if (st == nullptr || waits) return true;
-    return pl->work >= 4e9 && pl->work - pl->work_most >= pl->work / 8;
+    double work = 0.0, most = 0.0;
+    for (const HostChunk &ch : pl->chunks) {
+        double w = 0.0;
+        for (const SubMeta &m : ch.meta) w += (double)m.np * m.np * m.np;
+        work += w;
+        most = std::max(most, w);
+    }
+    return work >= 4e9 && work - most >= work / 8;
 }
 
 static int side_resources(nolsm_plan *pl, size_t nlane) {

@@ -618,13 +618,6 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
         size_t beside = 0;
         for (const auto &ch : pl->chunks) beside += align256(ch.ws_used);
         pl->side = pl->sched == NOLSM_SCHED_GRAPH && pl->chunks.size() > 1 && beside <= ws_bytes;
-        pl->work = pl->work_most = 0.0;
-        for (const auto &ch : pl->chunks) {
-            double w = 0.0;
-            for (const SubMeta &m : ch.meta) w += (double)m.np * m.np * m.np;
-            pl->work += w;
-            pl->work_most = std::max(pl->work_most, w);
-        }
         if (pl->side) {
             size_t at = 0;
             for (auto &ch : pl->chunks) {

@@ -73,7 +73,6 @@ struct nolsm_plan {
     // its own): streams beside the call's, and the events that fork and join
     // them, held for one call's launches at a time
     bool side = false;
-    double work = 0.0, work_most = 0.0;   // padded rows^3 of all chunks and of the largest
     std::vector<void *> lanes, lane_events;
     std::mutex lane_mu;
     nolsm_profile prof = {};
