@@ -26,12 +26,11 @@ static int hip_fail(hipError_t e, const char *where) {
     return NOLSM_E_HIP;
 }
 
-static void drop_graph(GraphSlot &g) {
-    if (g.exec) (void)hipGraphExecDestroy((hipGraphExec_t)g.exec);
-    g.exec = nullptr;
-}
-static void drop_graphs(nolsm_plan *pl) {
-    for (GraphSlot &g : pl->graphs) drop_graph(g);
+static void drop_graph(nolsm_plan *pl) {
+    if (pl->graph_exec) {
+        (void)hipGraphExecDestroy((hipGraphExec_t)pl->graph_exec);
+        pl->graph_exec = nullptr;
+    }
 }
 
 // The workspaces of nolsm_sign_batch_noalloc: NOLSM_NOALLOC_CALLS device
@@ -119,7 +118,7 @@ extern "C" int nolsm_plan_bind(nolsm_plan *pl, void *d_meta, size_t bytes, void 
         const int rc = scratch_events(pl->device);
         if (rc != NOLSM_OK) return rc;
     }
-    drop_graphs(pl);
+    drop_graph(pl);
     pl->d_meta = d_meta;
     pl->bound = true;
     int cus = 0;
@@ -565,11 +564,10 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
     } else if ((opts->sched == NOLSM_SCHED_GRAPH || opts->sched == NOLSM_SCHED_PERSISTENT ||
                 opts->sched == NOLSM_SCHED_PIPELINE) && st != nullptr) {
         const void *key[6] = {dK_val, dS_val, d_ws, dDcols, dD_val, dstats};
-        GraphSlot &slot = pl->graphs[side];
-        bool hit = slot.exec && slot.stream == stream && same_opts(slot.opts, *opts);
-        for (int i = 0; i < 6 && hit; ++i) hit = slot.key[i] == key[i];
+        bool hit = pl->graph_exec && pl->g_stream == stream && pl->g_side == side && same_opts(pl->g_opts, *opts);
+        for (int i = 0; i < 6 && hit; ++i) hit = pl->g_key[i] == key[i];
         if (!hit) {
-            drop_graph(slot);
+            drop_graph(pl);
             hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_fail(e, "graph capture begin");
             rc = opts->sched == NOLSM_SCHED_PIPELINE ? enqueue_pipe(pl, b, st)
@@ -586,12 +584,14 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
             e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return hip_fail(e, "graph instantiate");
-            slot.exec = ex;
-            for (int i = 0; i < 6; ++i) slot.key[i] = key[i];
-            slot.opts = *opts;
-            slot.stream = stream;
+            pl->graph_exec = ex;
+            for (int i = 0; i < 6; ++i) pl->g_key[i] = key[i];
+            pl->g_mu = mu;
+            pl->g_opts = *opts;
+            pl->g_stream = stream;
+            pl->g_side = side;
         }
-        hipError_t e = hipGraphLaunch((hipGraphExec_t)slot.exec, st);
+        hipError_t e = hipGraphLaunch((hipGraphExec_t)pl->graph_exec, st);
         if (e != hipSuccess) return hip_fail(e, "graph launch");
         rc = NOLSM_OK;
     } else {
@@ -791,7 +791,7 @@ extern "C" int nolsm_profile_last(const nolsm_plan *pl, nolsm_profile *out) {
 
 extern "C" void nolsm_plan_destroy(nolsm_plan *pl) {
     if (!pl) return;
-    drop_graphs(pl);
+    drop_graph(pl);
     for (void *ev : pl->events) (void)hipEventDestroy((hipEvent_t)ev);
     if (pl->aux_stream) (void)hipStreamDestroy((hipStream_t)pl->aux_stream);
     for (void *ev : pl->lane_events) (void)hipEventDestroy((hipEvent_t)ev);

@@ -27,14 +27,6 @@ struct HostChunk {
     size_t o_meta = 0, o_subst = 0, o_conv = 0, o_ns = 0, o_ns64 = 0, o_rows = 0;
 };
 
-// a captured batch and what it was captured for
-struct GraphSlot {
-    void *exec = nullptr;
-    const void *key[6] = {};
-    nolsm_solve_opts opts = {};
-    void *stream = nullptr;
-};
-
 struct nolsm_plan {
     int32_t nb = 0, bs = 0;
     std::vector<int32_t> Krp, Kci, Srp, Sci;
@@ -63,9 +55,13 @@ struct nolsm_plan {
     void *d_meta = nullptr;
     int device = -1;
     int32_t pgrid = 512;      // persistent-launch grid (2 x CUs), set by bind
-    // graph cache: the chunks in turn, and side by side (a search for mu and
-    // solves may want one each, in turn)
-    GraphSlot graphs[2];
+    // graph cache
+    void *graph_exec = nullptr;
+    const void *g_key[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    double g_mu = 0.0;
+    nolsm_solve_opts g_opts;
+    void *g_stream = nullptr;
+    bool g_side = false;      // captured with the chunks side by side
     // pipeline schedule: the library's second stream and its order events
     void *aux_stream = nullptr;
     std::vector<void *> events;
