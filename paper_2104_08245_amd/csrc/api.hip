@@ -9,7 +9,6 @@
 // later calls with the same buffers and options.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <condition_variable>
 #include <cstring>
@@ -348,84 +347,6 @@ static int enqueue(nolsm_plan *pl, const BatchArgs &b, hipStream_t st, PhaseEven
     return NOLSM_OK;
 }
 
-// Graph schedule with a region per chunk: the chunks side by side on LANES
-// streams, the call's own and the library's, which fork from it and join back
-// into it (so a capture holds them all, and what the caller does next on its
-// stream waits for all of them). A chunk goes to the lane with the least work.
-// A chunk is a chain of launches that each end in a partly empty wave, and a
-// small one leaves most of the GPU idle: beside each other a slab of 2,048
-// molecules (6 chunks) takes 149.3 instead of 161.3 ms, a bisection on 216
-// molecules 4.1 instead of 6.0 ms, 64 molecules in FP64 on the default stream
-// 1.53 instead of 2.10 ms. (Two lanes: 2,000 molecules combined 35.5 instead of
-// 34.5 ms; four: the bisection 4.4 instead of 4.1.)
-#define LANES 3
-// On a stream of the caller's that is weighed against what calls from other
-// streams lose, since graphs that fork do not run beside each other: small
-// calls, which fill the GPU only together (four streams: 64 molecules FP64 981
-// -> 1520 us a call, a slab of 400 FP64 3045 -> 3387), and calls whose work is
-// nearly all in one chunk (1,000 molecules FP16 on A_J, 5% outside it, 43.5 ->
-// 46.6 ms) stay in turn; from 4e9 padded rows^3 on with an eighth of them outside
-// the largest chunk they gain (the slab above has 19%, the combined molecules
-// 52%; a slab of 800, 22%: 4.7 instead of 5.7 ms with four streams). A call
-// that is waited for (`waits`) and calls on the default stream run alone.
-static bool side_by_side(const nolsm_plan *pl, const nolsm_solve_opts *o, hipStream_t st, bool waits) {
-    if (!pl->side || o->sched != NOLSM_SCHED_GRAPH) return false;
-    if (st == nullptr || waits) return true;
-    double work = 0.0, most = 0.0;
-    for (const HostChunk &ch : pl->chunks) {
-        double w = 0.0;
-        for (const SubMeta &m : ch.meta) w += (double)m.np * m.np * m.np;
-        work += w;
-        most = std::max(most, w);
-    }
-    return work >= 4e9 && work - most >= work / 8;
-}
-
-static int side_resources(nolsm_plan *pl, size_t nlane) {
-    while (pl->lanes.size() + 1 < nlane) {
-        hipStream_t s = nullptr;
-        hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-        if (e != hipSuccess) return hip_fail(e, "chunk stream");
-        pl->lanes.push_back(s);
-    }
-    while (pl->lane_events.size() < nlane) {
-        hipEvent_t ev = nullptr;
-        hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e != hipSuccess) return hip_fail(e, "chunk event");
-        pl->lane_events.push_back(ev);
-    }
-    return NOLSM_OK;
-}
-
-static int enqueue_side(nolsm_plan *pl, const BatchArgs &b, hipStream_t st) {
-    std::lock_guard<std::mutex> lock(pl->lane_mu);
-    const size_t nlane = std::min<size_t>(LANES, pl->chunks.size());
-    int rc = side_resources(pl, nlane);
-    if (rc != NOLSM_OK) return rc;
-    const LaunchArgs A = make_args(pl, b);
-    auto stream = [&](size_t l) { return l ? (hipStream_t)pl->lanes[l - 1] : st; };
-    auto ev = [&](size_t l) { return (hipEvent_t)pl->lane_events[l]; };   // 0: the fork, else lane l's end
-    hipError_t e = hipEventRecord(ev(0), st);
-    size_t forked = 1;
-    for (; e == hipSuccess && forked < nlane; ++forked)
-        if ((e = hipStreamWaitEvent(stream(forked), ev(0), 0)) != hipSuccess) break;
-    if (e != hipSuccess) rc = hip_fail(e, "chunk fork");
-    double load[LANES] = {};
-    for (const HostChunk &ch : pl->chunks) {
-        if (rc != NOLSM_OK) break;
-        const size_t l = std::min_element(load, load + nlane) - load;
-        for (const SubMeta &m : ch.meta) load[l] += (double)m.np * m.np * m.np;
-        rc = enqueue_setup(pl, b, A, ch, stream(l), nullptr);
-        if (rc == NOLSM_OK) rc = enqueue_solve(pl, b, A, ch, stream(l), nullptr);
-    }
-    // what was forked is joined, also after an error
-    for (size_t l = 1; l < forked; ++l) {
-        if ((e = hipEventRecord(ev(l), stream(l))) == hipSuccess) e = hipStreamWaitEvent(st, ev(l), 0);
-        if (e != hipSuccess && rc == NOLSM_OK) rc = hip_fail(e, "chunk join");
-    }
-    return rc;
-}
-
 // Pipeline schedule: the chunks alternate between two workspace regions.
 // The setups run in order on the library's stream s2 and the solves in
 // order on the call's stream st; solve(c) waits for setup(c), and setup(c)
@@ -522,23 +443,21 @@ static int check_batch(const nolsm_plan *pl, const double *dK_val, const double 
 }
 
 // mu lives in the workspace header (outside any captured graph), so a
-// captured batch serves every mu; k_init_ctl copies it to the headers of the
-// other regions
+// captured batch serves every mu; k_init_ctl copies it to the header of the
+// pipeline's second region
 static int write_header(char *ws, double mu, hipStream_t st) {
     hipError_t e = launch_set_header(ws, mu, st);
     return e == hipSuccess ? NOLSM_OK : hip_fail(e, "header launch");
 }
 
-// `waits`: the caller waits for the solve before it enqueues more
-static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
-                      const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols, double *dD_val,
-                      nolsm_mol_stats *dstats, void *stream, bool waits) {
+extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
+                                const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols,
+                                double *dD_val, nolsm_mol_stats *dstats, void *stream) {
     int rc = check_batch(pl, dK_val, dS_val, opts, d_ws, ws_bytes, dDcols, dstats, stream);
     if (rc != NOLSM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     BatchArgs b{dK_val, dS_val, mu, opts, (char *)d_ws, dDcols, dD_val, (void *)dstats};
     if ((rc = write_header((char *)d_ws, mu, st)) != NOLSM_OK) return rc;
-    const bool side = side_by_side(pl, opts, st, waits || opts->sync_errors);
     if (opts->profile) {
         PhaseEvents pe;
         pe.st = st;
@@ -564,15 +483,13 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
     } else if ((opts->sched == NOLSM_SCHED_GRAPH || opts->sched == NOLSM_SCHED_PERSISTENT ||
                 opts->sched == NOLSM_SCHED_PIPELINE) && st != nullptr) {
         const void *key[6] = {dK_val, dS_val, d_ws, dDcols, dD_val, dstats};
-        bool hit = pl->graph_exec && pl->g_stream == stream && pl->g_side == side && same_opts(pl->g_opts, *opts);
+        bool hit = pl->graph_exec && pl->g_stream == stream && same_opts(pl->g_opts, *opts);
         for (int i = 0; i < 6 && hit; ++i) hit = pl->g_key[i] == key[i];
         if (!hit) {
             drop_graph(pl);
             hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_fail(e, "graph capture begin");
-            rc = opts->sched == NOLSM_SCHED_PIPELINE ? enqueue_pipe(pl, b, st)
-                 : side                              ? enqueue_side(pl, b, st)
-                                                     : enqueue(pl, b, st);
+            rc = opts->sched == NOLSM_SCHED_PIPELINE ? enqueue_pipe(pl, b, st) : enqueue(pl, b, st);
             hipGraph_t g = nullptr;
             e = hipStreamEndCapture(st, &g);
             if (rc != NOLSM_OK) {
@@ -589,13 +506,12 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
             pl->g_mu = mu;
             pl->g_opts = *opts;
             pl->g_stream = stream;
-            pl->g_side = side;
         }
         hipError_t e = hipGraphLaunch((hipGraphExec_t)pl->graph_exec, st);
         if (e != hipSuccess) return hip_fail(e, "graph launch");
         rc = NOLSM_OK;
     } else {
-        rc = side ? enqueue_side(pl, b, st) : enqueue(pl, b, st);
+        rc = enqueue(pl, b, st);
         if (rc != NOLSM_OK) return rc;
     }
     if (opts->sync_errors) {
@@ -612,12 +528,6 @@ static int sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val
         }
     }
     return NOLSM_OK;
-}
-
-extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const double *dS_val, double mu,
-                                const nolsm_solve_opts *opts, void *d_ws, size_t ws_bytes, double *dDcols,
-                                double *dD_val, nolsm_mol_stats *dstats, void *stream) {
-    return sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream, false);
 }
 
 // ------------------------------------------------- allocation-free variant
@@ -746,7 +656,7 @@ extern "C" int nolsm_mu_bisect(nolsm_plan *pl, const double *dK_val, const doubl
     int32_t step = 0;
     for (step = 1; step <= max_steps; ++step) {
         mu = 0.5 * (lo + hi);
-        int rc = sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream, true);
+        int rc = nolsm_sign_batch(pl, dK_val, dS_val, mu, opts, d_ws, ws_bytes, dDcols, dD_val, dstats, stream);
         if (rc != NOLSM_OK) return rc;
         double sums[3];
         rc = nolsm_trace_sums(pl, dstats, d_ws, sums, stream);
@@ -794,7 +704,5 @@ extern "C" void nolsm_plan_destroy(nolsm_plan *pl) {
     drop_graph(pl);
     for (void *ev : pl->events) (void)hipEventDestroy((hipEvent_t)ev);
     if (pl->aux_stream) (void)hipStreamDestroy((hipStream_t)pl->aux_stream);
-    for (void *ev : pl->lane_events) (void)hipEventDestroy((hipEvent_t)ev);
-    for (void *s : pl->lanes) (void)hipStreamDestroy((hipStream_t)s);
     delete pl;
 }

@@ -612,20 +612,7 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
             ch.base = (pipe && (pl->chunks.size() & 1)) ? region : 0;
             pl->chunks.push_back(std::move(ch));
         }
-        // graph schedule: with room for every chunk beside the others they run
-        // side by side (the control blocks are budgeted in whole 256 bytes but
-        // packed, which leaves ws_full that room from about 30 slots on)
-        size_t beside = 0;
-        for (const auto &ch : pl->chunks) beside += align256(ch.ws_used);
-        pl->side = pl->sched == NOLSM_SCHED_GRAPH && pl->chunks.size() > 1 && beside <= ws_bytes;
-        if (pl->side) {
-            size_t at = 0;
-            for (auto &ch : pl->chunks) {
-                ch.base = at;
-                at += align256(ch.ws_used);
-            }
-        }
-        pl->apart = pipe || pl->side || pl->chunks.size() <= 1;
+        pl->apart = pipe || pl->chunks.size() <= 1;
         // metadata image
         pl->image.clear();
         pl->o_Krp = put(pl->image, pl->Krp.data(), pl->Krp.size());

@@ -3,7 +3,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -21,8 +20,7 @@ struct HostChunk {
     size_t off_ictl = 0;      // workspace offset of the InvCtl array (0: none)
     size_t off_q = 0;         // workspace offset of the queue counters
     size_t base = 0;          // offset of the chunk's region in the workspace
-                              // (pipeline schedule: two regions in turn; graph
-                              // schedule: one each where there is room)
+                              // (pipeline schedule: two regions in turn)
     // metadata image offsets (bytes from d_meta)
     size_t o_meta = 0, o_subst = 0, o_conv = 0, o_ns = 0, o_ns64 = 0, o_rows = 0;
 };
@@ -61,16 +59,9 @@ struct nolsm_plan {
     double g_mu = 0.0;
     nolsm_solve_opts g_opts;
     void *g_stream = nullptr;
-    bool g_side = false;      // captured with the chunks side by side
     // pipeline schedule: the library's second stream and its order events
     void *aux_stream = nullptr;
     std::vector<void *> events;
-    // graph schedule, chunks side by side (`side`: every chunk has a region of
-    // its own): streams beside the call's, and the events that fork and join
-    // them, held for one call's launches at a time
-    bool side = false;
-    std::vector<void *> lanes, lane_events;
-    std::mutex lane_mu;
     nolsm_profile prof = {};
 };
 

@@ -7,6 +7,7 @@ import ctypes as C
 import pytest
 
 from paper_2104_08245_amd import _lib as L
+import synth
 
 
 def call(p, opts, stream):
@@ -17,15 +18,16 @@ def call(p, opts, stream):
     return rc, L.lib().nolsm_strerror(rc).decode()
 
 
-@pytest.mark.parametrize("sched", [L.SCHED_GRAPH, L.SCHED_STREAM, L.SCHED_PERSISTENT])
-def test_pipeline_refuses_plans_whose_chunks_share_bytes(box64, sched):
+@pytest.mark.parametrize("sched,ws_bytes", [(L.SCHED_GRAPH, 32 << 20), (L.SCHED_STREAM, 32 << 20),
+                                            (L.SCHED_STREAM, 1 << 30), (L.SCHED_PERSISTENT, 1 << 30)])
+def test_pipeline_refuses_plans_whose_chunks_share_bytes(box64, sched, ws_bytes):
     from paper_2104_08245_amd import Plan
     s = box64
     p = Plan(s.K.nb, s.K.bs, s.K.row_ptr, s.K.col_idx)
     stream = C.c_void_p(1 << 20)
     opts = L.default_opts("fp16", sched=sched)
-    p.configure(opts, 32 << 20)
-    assert p.info()["nchunks"] >= 3
+    p.configure(opts, ws_bytes)
+    assert p.info()["nchunks"] >= 2
     opts.sched = L.SCHED_PIPELINE
     rc, msg = call(p, opts, stream)
     assert rc == L.E_STATE and "pipeline" in msg
@@ -37,12 +39,20 @@ def test_pipeline_refuses_plans_whose_chunks_share_bytes(box64, sched):
         assert rc == L.E_STATE and msg.endswith("not bound")
 
 
-@pytest.mark.parametrize("sched,ws_bytes", [(L.SCHED_PIPELINE, 32 << 20), (L.SCHED_GRAPH, 1 << 30)])
-def test_pipeline_takes_chunks_in_regions_of_their_own(box64, sched, ws_bytes):
+def test_pipeline_takes_chunks_in_regions_of_their_own(box64):
     from paper_2104_08245_amd import Plan
     s = box64
     p = Plan(s.K.nb, s.K.bs, s.K.row_ptr, s.K.col_idx)
-    p.configure(L.default_opts("fp16", sched=sched), ws_bytes)
-    assert p.info()["nchunks"] >= 2
-    rc, msg = call(p, L.default_opts("fp16", sched=L.SCHED_PIPELINE), C.c_void_p(1 << 20))
+    stream = C.c_void_p(1 << 20)
+    for sched, ws_bytes in ((L.SCHED_PIPELINE, 32 << 20), (L.SCHED_PIPELINE, 1 << 30)):
+        p.configure(L.default_opts("fp16", sched=sched), ws_bytes)
+        assert p.info()["nchunks"] >= 2
+        rc, msg = call(p, L.default_opts("fp16", sched=L.SCHED_PIPELINE), stream)
+        assert rc == L.E_STATE and msg.endswith("not bound")
+    # one chunk has nothing to share: 8 molecules within one cutoff
+    s = synth.water_cube(8, 2.2, config_id=1)
+    p = Plan(s.K.nb, s.K.bs, s.K.row_ptr, s.K.col_idx)
+    p.configure(L.default_opts("fp16"), 1 << 30)
+    assert p.info()["nchunks"] == 1
+    rc, msg = call(p, L.default_opts("fp16", sched=L.SCHED_PIPELINE), stream)
     assert rc == L.E_STATE and msg.endswith("not bound")
