@@ -262,7 +262,10 @@ typedef struct {
     int64_t sum_m;           /* sum_J m_J = nnzb(D) = number of Dcols blocks      */
     int32_t m_min, m_max;    /* blocks per submatrix                              */
     double sum_n3;           /* sum_J n_J^3 (true sizes)                          */
-    int32_t nchunks;         /* after nolsm_plan_configure, else 0                */
+    int32_t nchunks;         /* after nolsm_plan_configure, else 0: chunks of
+                                submatrices of similar size that the workspace
+                                holds together (with NOLSM_SCHED_GRAPH small ones
+                                that follow each other share their launches)     */
     size_t meta_bytes;       /* device metadata bytes needed by nolsm_plan_bind   */
     size_t ws_min_bytes;     /* smallest workspace that holds the largest J       */
     size_t ws_full_bytes;    /* workspace holding the whole batch in one chunk    */

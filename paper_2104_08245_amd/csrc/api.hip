@@ -150,7 +150,6 @@ static ChunkDev chunk_dev(const nolsm_plan *pl, const HostChunk &ch, char *ws) {
     cd.max_m = ch.max_m;
     cd.max_np = ch.max_np;
     cd.max_own = ch.max_own;
-    cd.ns_wide = ch.ns_wide ? 1 : 0;
     return cd;
 }
 
@@ -476,7 +475,7 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
         if (pe.ev.size() >= 2) (void)hipEventElapsedTime(&tot, pe.ev.front(), pe.ev.back());
         p.ms_total = tot;
         p.valid = 1;
-        p.nchunks = (int32_t)pl->chunks.size();
+        p.nchunks = pl->nchunks;
         p.n_ns_launches = pe.n_ns;
         p.n_fin_launches = pe.n_fin;
         pl->prof = p;

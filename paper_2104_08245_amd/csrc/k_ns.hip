@@ -141,9 +141,9 @@ template <typename T, int NC> struct Ns64Tile {
 // matrix core busy from two waves on (four chains a wave reached 125 of 155
 // TF/s in FP32 with four waves): 512 submatrices of about 612 rows in FP64
 // 4433 us a launch against 4834 with NC = 2 (5938 before the slices were
-// fetched ahead), 777 in FP32 3296 against 3716 (3850). NC = 2 serves chunks
-// too small to fill the GPU with the wider tiles (plan.cpp). The next slice
-// is fetched into registers while this one is multiplied from LDS. The
+// fetched ahead), 777 in FP32 3296 against 3716 (3850). NC = 2 serves size
+// ranges with too few of the wider tiles to fill the GPU. The next slice is
+// fetched into registers while this one is multiplied from LDS. The
 // contraction stops at n (X_k and R are identity and zero on the padding,
 // whose products are exact zeros), and the padding of a result is set rather
 // than computed.
@@ -303,9 +303,9 @@ __device__ __forceinline__ int queue_pop(int *q, int *slot) {
 }
 
 template <typename T, int NC>
-__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64(ChunkDev cd, char *ws, NsArgs na, int it,
-                                                                    int mode) {
-    ns64_tile<T, NC>(cd, xcd_task(cd.t_ns), ws, na, it, mode);
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64(ChunkDev cd, const uint32_t *tasks, char *ws,
+                                                                    NsArgs na, int it, int mode) {
+    ns64_tile<T, NC>(cd, xcd_task(tasks), ws, na, it, mode);
 }
 
 // the slots that a scanning launch still has to work on
@@ -388,13 +388,15 @@ __device__ __forceinline__ void rest_of(SubCtl *ctl, int nt, int bstep, int it0,
     __syncthreads();
 }
 template <typename T, int NC>
-__global__ __launch_bounds__(256, 2) void k_ns64_tail(ChunkDev cd, char *ws, NsArgs na, int it, int mode) {
-    scan_tasks(cd.t_ns, cd.n_ns, iterating(cd), [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
+__global__ __launch_bounds__(256, 2) void k_ns64_tail(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws, NsArgs na,
+                                                    int it, int mode) {
+    scan_tasks(tasks, ntask, iterating(cd), [&](uint32_t task) { ns64_tile<T, NC>(cd, task, ws, na, it, mode); });
 }
 
 template <typename T, int NC>
-__global__ __launch_bounds__(256, 2) void k_ns64_rest(ChunkDev cd, char *ws, NsArgs na, int it0) {
-    scan_tasks(cd.t_ns, cd.n_ns, iterating(cd), [&](uint32_t task) {
+__global__ __launch_bounds__(256, 2) void k_ns64_rest(ChunkDev cd, const uint32_t *tasks, int ntask, char *ws, NsArgs na,
+                                                    int it0) {
+    scan_tasks(tasks, ntask, iterating(cd), [&](uint32_t task) {
         const int s = task_slot(task);
         rest_of<false>(cd.ctl + s, cd.meta[s].np / 64, NC / 2, it0, na.max_iter, [&](int a, int b, int it, int mode) {
             ns64_tile<T, NC>(cd, NOLSM_TASK(s, a, b), ws, na, it, mode);
@@ -403,14 +405,14 @@ __global__ __launch_bounds__(256, 2) void k_ns64_rest(ChunkDev cd, char *ws, NsA
 }
 
 template <typename T, int NC>
-__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64_pq(ChunkDev cd, int ntask, int *q, char *ws,
-                                                                       NsArgs na, int it, int mode) {
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 3) void k_ns64_pq(ChunkDev cd, const uint32_t *tasks, int ntask,
+                                                                       int *q, char *ws, NsArgs na, int it, int mode) {
     __shared__ int idx_s;
     const int x = blockIdx.x & 7, seg = ntask >> 3;
     for (;;) {
         const int i = queue_pop(q + x, &idx_s);
         if (i >= seg) break;
-        ns64_tile<T, NC>(cd, cd.t_ns[x * seg + i], ws, na, it, mode);
+        ns64_tile<T, NC>(cd, tasks[x * seg + i], ws, na, it, mode);
     }
 }
 
@@ -651,22 +653,25 @@ static void launch_lp(const ChunkDev &cd, char *ws, NsArgs na, int it, int mode,
 }
 
 template <typename T, int NC>
-static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
+static void launch_64(const ChunkDev &cd, const uint32_t *tasks, int ntask, char *ws, const NsArgs &na, int it, int mode,
+                      hipStream_t st) {
+    if (ntask <= 0) return;
     if (na.persistent)
-        hipLaunchKernelGGL((k_ns64_pq<T, NC>), dim3(persistent_grid(na, cd.n_ns)), dim3(256), 0, st, cd, cd.n_ns,
-                           launch_queue(cd, it, mode, 0), ws, na, it, mode);
+        hipLaunchKernelGGL((k_ns64_pq<T, NC>), dim3(persistent_grid(na, ntask)), dim3(256), 0, st, cd, tasks, ntask,
+                           launch_queue(cd, it, mode, NC == 2), ws, na, it, mode);
     else if (it < NS64_TAIL_IT)
-        hipLaunchKernelGGL((k_ns64<T, NC>), dim3(cd.n_ns), dim3(256), 0, st, cd, ws, na, it, mode);
-    else if (it < NS64_REST_IT || !rest_chunk(na, cd.n_ns))
-        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na.pgrid, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it, mode);
+        hipLaunchKernelGGL((k_ns64<T, NC>), dim3(ntask), dim3(256), 0, st, cd, tasks, ws, na, it, mode);
+    else if (it < NS64_REST_IT || !rest_chunk(na, ntask))
+        hipLaunchKernelGGL((k_ns64_tail<T, NC>), dim3(scan_grid(na.pgrid, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+                           na, it, mode);
     else if (it == NS64_REST_IT && mode == 1)
-        hipLaunchKernelGGL((k_ns64_rest<T, NC>), dim3(scan_grid(na.pgrid, cd.n_ns)), dim3(256), 0, st, cd, ws, na, it);
+        hipLaunchKernelGGL((k_ns64_rest<T, NC>), dim3(scan_grid(na.pgrid, ntask)), dim3(256), 0, st, cd, tasks, ntask, ws,
+                           na, it);
 }
 template <typename T>
 static void launch_64(const ChunkDev &cd, char *ws, const NsArgs &na, int it, int mode, hipStream_t st) {
-    if (cd.n_ns <= 0) return;
-    if (cd.ns_wide) launch_64<T, 4>(cd, ws, na, it, mode, st);
-    else launch_64<T, 2>(cd, ws, na, it, mode, st);
+    launch_64<T, 4>(cd, cd.t_ns, cd.n_ns, ws, na, it, mode, st);
+    launch_64<T, 2>(cd, cd.t_ns64, cd.n_ns64, ws, na, it, mode, st);
 }
 
 hipError_t launch_ns_iter(const ChunkDev &cd, char *ws, const NsArgs &na, int it, hipStream_t st) {

@@ -95,14 +95,13 @@ struct ChunkDev {
     const SubMeta *meta;
     const uint32_t *t_subst;   // (slot, column tile 0..P)
     const uint32_t *t_conv;    // (slot, 64x64 tile i, j) for X_0
-    const uint32_t *t_ns;      // (slot, NS tile i, j): 64x64 (FP64/FP32; ns_wide: 64x128, j even) or
-                               // 128x128 (FP16/BF16) tiles
-    const uint32_t *t_ns64;    // FP16/BF16 slots that use 64x64 tiles
+    const uint32_t *t_ns;      // (slot, NS tile i, j): 128x128 tiles (FP16/BF16), or 64x128, j even
+                               // (FP64/FP32)
+    const uint32_t *t_ns64;    // slots that use 64x64 tiles
     const uint32_t *t_rows;    // (slot, 256-row block, owned molecule) for the skinny products
     SubCtl *ctl;               // in the workspace
     InvCtl *ictl;              // in the workspace (coupled inverse), else null
     int32_t *queues;           // persistent launches: [max_iter][2][2][8] counters
     int32_t nqueue;            // number of counters
     int32_t nsub, n_subst, n_conv, n_ns, n_ns64, n_rows, max_m, max_np, max_own;
-    int32_t ns_wide;           // FP64/FP32: a task takes two 64-column tiles
 };

@@ -353,7 +353,7 @@ extern "C" int nolsm_plan_info(const nolsm_plan *p, nolsm_plan_sizes *o) {
     o->m_max = p->m_max;
     o->sum_n3 = p->sum_n3;
     if (p->configured) {
-        o->nchunks = (int32_t)p->chunks.size();
+        o->nchunks = p->nchunks;
         o->meta_bytes = p->image.size();
         o->ws_min_bytes = p->ws_min;
         o->ws_full_bytes = p->ws_full;
@@ -493,20 +493,42 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
         // cut where np falls below 4/5 of the chunk's largest, because the
         // serial setup launches (Cholesky panels, right-solve row blocks) of
         // a chunk run to the depth of its largest submatrix while smaller
-        // ones idle
+        // ones idle. The graph schedule launches chunks that follow each other
+        // together where one of them has too few submatrices to fill the GPU
+        // (FILL, half its CUs), since each chain of launches costs its length
+        // (64 molecules, 7 submatrices of 256 rows and 57 of 192: 494 -> 391 us
+        // in FP16, 2165 -> 1561 in FP64; a bisection on 216 molecules, 211 and
+        // 5, 5.6 -> 4.0 ms; 208 molecules combined, 7, 33 and 49, 3.5 -> 2.5).
+        // Beyond that it gains little or loses (three streams of slabs of
+        // 2,048 molecules, with six ranges of 63 to 791: 152.3 ms a solve with
+        // each by itself, 151.9 with FILL 128, 157.3 with 256).
+        const size_t FILL = 128;
+        const bool share = pl->sched == NOLSM_SCHED_GRAPH;
+        auto range_end = [&](size_t from) {   // of the size range that begins there
+            size_t e = from;
+            while (e < order.size() && 5 * np_of(order[e]) >= 4 * np_of(order[from])) ++e;
+            return e;
+        };
+        pl->nchunks = 0;
         size_t i = 0;
         while (i < order.size()) {
             HostChunk ch;
             size_t used = 0;
             std::vector<int32_t> js;
-            const int32_t bucket = np_of(order[i]);
+            std::vector<size_t> first;   // slot at which each of its size ranges begins
+            int32_t lead = 0;            // rows of the range's largest
             while (i < order.size() && js.size() < 65535) {
                 const int32_t J = order[i];
-                if (pl->sched == NOLSM_SCHED_PER_BUCKET && np_of(J) != bucket) break;
-                if (pl->sched != NOLSM_SCHED_PER_BUCKET && 5 * np_of(J) < 4 * bucket) break;
+                const bool next = js.empty() || (pl->sched == NOLSM_SCHED_PER_BUCKET ? np_of(J) != lead
+                                                                                     : 5 * np_of(J) < 4 * lead);
+                if (next && !js.empty() && !(share && (js.size() < FILL || range_end(i) - i < FILL))) break;
                 const size_t sb = slot_bytes(J);
                 if (used + sb + 256 + qbytes > region) break;
                 used += sb;
+                if (next) {
+                    first.push_back(js.size());
+                    lead = np_of(J);
+                }
                 js.push_back(J);
                 ++i;
             }
@@ -521,20 +543,25 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                 ch.off_q += align256(js.size() * sizeof(InvCtl));
             }
             // FP64/FP32: tasks of two 64-column tiles run the matrix cores
-            // fuller, but only where they still give every CU its two
-            // workgroups twice over (256 CUs); a smaller chunk is bound by
-            // the time of one task
-            if (pl->prec == NOLSM_FP64 || pl->prec == NOLSM_FP32) {
+            // fuller, but only where those of a size range still give every
+            // CU its two workgroups twice over (256 CUs); a smaller range is
+            // bound by the time of one task
+            const bool plain = pl->prec == NOLSM_FP64 || pl->prec == NOLSM_FP32;
+            auto wide_range = [&](size_t r) {
+                const size_t end = r + 1 < first.size() ? first[r + 1] : js.size();
                 size_t wide = 0;
-                for (int32_t g : js) {
-                    const size_t nt = (size_t)np_of(g) / NOLSM_TILE;
+                for (size_t s = first[r]; s < end; ++s) {
+                    const size_t nt = (size_t)np_of(js[s]) / NOLSM_TILE;
                     wide += nt * ((nt + 1) / 2);
                 }
-                ch.ns_wide = wide >= 1024;
-            }
-            size_t off = ch.off_q + qbytes;
+                return wide >= 1024;
+            };
+            pl->nchunks += (int32_t)first.size();
+            size_t off = ch.off_q + qbytes, range = 0;
+            bool wide = plain && wide_range(0);
             for (size_t s = 0; s < js.size(); ++s) {
                 const int32_t g = js[s];
+                if (range + 1 < first.size() && s == first[range + 1]) wide = plain && wide_range(++range);
                 SubMeta m;
                 std::memset(&m, 0, sizeof(m));
                 m.J = pl->own_J[pl->own_ptr[g]];
@@ -587,12 +614,12 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
                 // also writes its mirror where that is stored)
                 for (int32_t a = 0; a < m.P; ++a)
                     for (int32_t b = pl->sym ? a : 0; b < m.P; ++b) ch.t_conv.push_back(NOLSM_TASK(s, a, b));
-                // FP16/BF16 slots with 64-row tiles get their own list
-                std::vector<uint32_t> &tl =
-                    (T == 64 && (pl->prec == NOLSM_FP16 || pl->prec == NOLSM_BF16)) ? ch.t_ns64 : ch.t_ns;
+                // slots with 64-row tiles (FP16/BF16), or tasks of one tile
+                // (FP64/FP32), have their own list
+                std::vector<uint32_t> &tl = T == 64 && !wide ? ch.t_ns64 : ch.t_ns;
                 // symmetric route: upper tiles only
                 const bool sym = pl->sym != 0;
-                const int32_t bstep = ch.ns_wide ? 2 : 1;
+                const int32_t bstep = wide ? 2 : 1;
                 for (int32_t a = 0; a < nt; ++a)
                     for (int32_t b = sym ? a : 0; b < nt; b += bstep) tl.push_back(NOLSM_TASK(s, a, b));
                 // (slot, 256-row block, owned molecule): the molecules of one row

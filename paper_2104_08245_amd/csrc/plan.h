@@ -14,7 +14,6 @@ struct HostChunk {
     std::vector<uint32_t> t_subst, t_conv, t_ns, t_ns64, t_rows;
     int32_t max_m = 0, max_np = 0, max_own = 1;
     size_t n_ns_real = 0, n_ns64_real = 0;   // task counts before padding
-    bool ns_wide = false;     // FP64/FP32: tasks of two 64-column tiles
     size_t ws_used = 0;       // bytes of the workspace this chunk uses
     size_t off_ctl = 0;       // workspace offset of the SubCtl array
     size_t off_ictl = 0;      // workspace offset of the InvCtl array (0: none)
@@ -45,7 +44,8 @@ struct nolsm_plan {
     int32_t prec = -1, sched = -1, max_iter = 0, ns_tile = 0, elem = 0;
     int32_t inverse = 0, inv_max_iter = 0, sym = 0;
     size_t ws_bytes = 0, ws_min = 0, ws_full = 0;
-    std::vector<HostChunk> chunks;
+    std::vector<HostChunk> chunks;        // those launched together as one
+    int32_t nchunks = 0;
     bool apart = false;                   // chunks that follow each other share no workspace bytes
     std::vector<char> image;              // metadata image uploaded by bind
     size_t o_Krp = 0, o_Kci = 0, o_Srp = 0, o_Sci = 0, o_sub_ptr = 0, o_sub_blk = 0,
