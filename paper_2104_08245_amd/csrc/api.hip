@@ -39,8 +39,8 @@ static void drop_graph(nolsm_plan *pl) {
 // taken longest ago, and its stream waits for the end of the call that had it.
 // So calls of one stream stay in one array, and up to NOLSM_NOALLOC_CALLS
 // streams run side by side: a small solve leaves most of the GPU idle (calls on
-// three streams in turn, 64 molecules in FP64 1225 us a call, 25 in FP16 249;
-// 2672 and 792 with one array, where each waited for the one before). An array
+// three streams in turn, 64 molecules in FP64 1020 us a call, 25 in FP16 300;
+// 1815 and 580 one after the other on one stream). An array
 // belongs to one call's launches at a time. Calls under a caller's capture,
 // whose replays the library does not see, use the first and take no part in
 // the order.

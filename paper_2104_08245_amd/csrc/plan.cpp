@@ -502,37 +502,55 @@ extern "C" int nolsm_plan_configure(nolsm_plan *pl, const nolsm_solve_opts *opts
         // Beyond that it gains little or loses (three streams of slabs of
         // 2,048 molecules, with six ranges of 63 to 791: 152.3 ms a solve with
         // each by itself, 151.9 with FILL 128, 157.3 with 256).
+        // Where the workspace has not the room, that may leave as many chains,
+        // split worse: it is done only if it leaves fewer (64 molecules with
+        // 64 MB: FP16, two either way, 1297 us each by itself and 1445
+        // together, FP64, three and two, 2510 and 1815).
         const size_t FILL = 128;
-        const bool share = pl->sched == NOLSM_SCHED_GRAPH;
         auto range_end = [&](size_t from) {   // of the size range that begins there
             size_t e = from;
             while (e < order.size() && 5 * np_of(order[e]) >= 4 * np_of(order[from])) ++e;
             return e;
         };
-        pl->nchunks = 0;
-        size_t i = 0;
-        while (i < order.size()) {
-            HostChunk ch;
-            size_t used = 0;
-            std::vector<int32_t> js;
+        struct Cut {
+            size_t begin, end;
             std::vector<size_t> first;   // slot at which each of its size ranges begins
-            int32_t lead = 0;            // rows of the range's largest
-            while (i < order.size() && js.size() < 65535) {
-                const int32_t J = order[i];
-                const bool next = js.empty() || (pl->sched == NOLSM_SCHED_PER_BUCKET ? np_of(J) != lead
-                                                                                     : 5 * np_of(J) < 4 * lead);
-                if (next && !js.empty() && !(share && (js.size() < FILL || range_end(i) - i < FILL))) break;
-                const size_t sb = slot_bytes(J);
-                if (used + sb + 256 + qbytes > region) break;
-                used += sb;
-                if (next) {
-                    first.push_back(js.size());
-                    lead = np_of(J);
+        };
+        auto cut = [&](bool share) {
+            std::vector<Cut> cuts;
+            for (size_t i = 0; i < order.size();) {
+                Cut c;
+                c.begin = i;
+                size_t used = 0;
+                int32_t lead = 0;   // rows of the range's largest
+                for (; i < order.size() && i - c.begin < 65535; ++i) {
+                    const int32_t np = np_of(order[i]);
+                    const size_t n = i - c.begin;
+                    const bool next = n == 0 || (pl->sched == NOLSM_SCHED_PER_BUCKET ? np != lead : 5 * np < 4 * lead);
+                    if (next && n > 0 && !(share && (n < FILL || range_end(i) - i < FILL))) break;
+                    const size_t sb = slot_bytes(order[i]);
+                    if (used + sb + 256 + qbytes > region) break;
+                    used += sb;
+                    if (next) {
+                        c.first.push_back(n);
+                        lead = np;
+                    }
                 }
-                js.push_back(J);
-                ++i;
+                c.end = i;
+                cuts.push_back(std::move(c));
             }
-            // layout: SubCtl array first, then the slots
+            return cuts;
+        };
+        std::vector<Cut> cuts = cut(false);
+        if (pl->sched == NOLSM_SCHED_GRAPH) {
+            std::vector<Cut> shared = cut(true);
+            if (shared.size() < cuts.size()) cuts = std::move(shared);
+        }
+        pl->nchunks = 0;
+        for (const Cut &c : cuts) {
+            HostChunk ch;
+            const std::vector<int32_t> js(order.begin() + c.begin, order.begin() + c.end);
+            const std::vector<size_t> &first = c.first;
             // layout: workspace header, SubCtl array, InvCtl array (coupled
             // inverse only), queue counters, slots
             ch.off_ctl = NOLSM_WS_HEADER;
