@@ -78,6 +78,14 @@ __device__ __forceinline__ void silu2(float z, float &h, float &d) {
     h = z * s;
     d = s * (1.0f + z * (1.0f - s));
 }
+// Between a wave's stores to its own LDS rows and other lanes' loads of them,
+// either way round: the wave's LDS accesses are executed in order, and this
+// keeps the compiler to it (no instruction comes of it).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 __device__ __forceinline__ float sum16(float v) {   // over the 16 lanes of a group
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -151,7 +159,8 @@ __global__ __launch_bounds__(NWAVE * 64) void k_mlp_loss_grad(const float *__res
                 if (j == g) dz1[e] = d;
                 A[(4 * lk + e) * LDW + 16 * j + li] = h;
             }
-        // layer 2 (the wave's own rows: its LDS accesses are in order)
+        wave_sync();
+        // layer 2
         f4 z2[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) z2[j] = (f4){b2[j], b2[j], b2[j], b2[j]};
@@ -201,10 +210,12 @@ __global__ __launch_bounds__(NWAVE * 64) void k_mlp_loss_grad(const float *__res
 #pragma unroll
                     for (int i = 0; i < 4; ++i) gW2[i] = mma4(gz2[i][e], h1[j][e], gW2[i]);
         // back through W2 to block g of layer 1
+        wave_sync();
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) A[(4 * lk + e) * LDW + 16 * j + li] = gz2[j][e];
+        wave_sync();
         f4 gh1 = {0, 0, 0, 0}, gh1b = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < 16; s += 2) {
@@ -218,6 +229,7 @@ __global__ __launch_bounds__(NWAVE * 64) void k_mlp_loss_grad(const float *__res
             const float xs = li < NF ? (b < B ? (x[(int64_t)b * NF + li] - xm) / xd : 0.0f) : (li == NF ? 1.0f : 0.0f);
             gW1 = mma4((gh1[e] + gh1b[e]) * dz1[e], xs, gW1);
         }
+        wave_sync();   // the next pass, or the sums, overwrite the rows
     }
     // the waves' sums side by side in LDS, then added in wave order
 #pragma unroll
