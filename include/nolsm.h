@@ -170,6 +170,7 @@ typedef struct {
     float mlp_safety;        /* c_J = 1/(safety * rho_hat); default 1.05         */
     int32_t sched;           /* nolsm_sched                                      */
     int32_t sync_errors;     /* != 0: synchronize and return E_NOT_SPD/E_NOCONV  */
+    int32_t debug_stall_it;  /* iteration of debug_force_stall; 0 (default): 2   */
     float *d_features;       /* optional device [nb][12] float: features of A_J
                                 (of L^-1 T_J(K) L^-T - mu I with sym_sign)       */
     double debug_scale_mult; /* != 0: multiply c_J (tests of the restart guard)  */
@@ -211,9 +212,10 @@ typedef struct {
                                 FP16 high and low parts). BF16 always uses the
                                 vector kernel. Default 0.                      */
     int32_t debug_force_stall;/* >= 0: molecule whose sign iteration is taken as
-                                diverged after its residual at iteration 2, so
-                                the guard restarts it from the Gershgorin scale
-                                (fallback = 1, same result); -1: none        */
+                                diverged after its residual at iteration
+                                debug_stall_it, so the guard restarts it from the
+                                Gershgorin scale (fallback = 1, same result);
+                                -1: none                                       */
     int32_t subst_fp32;      /* sym_sign with FP32 substitutions (the FP32
                                 factor, or the FP64 factor applied in FP32):
                                 != 0 forms their tile products on the FP32

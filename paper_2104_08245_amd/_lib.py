@@ -43,7 +43,7 @@ class SolveOpts(C.Structure):
                 ("switch_theta", C.c_double), ("switch_rmax", C.c_double),
                 ("bounds", C.c_int32), ("d_mlp", C.c_void_p), ("d_mlp_norm", C.c_void_p),
                 ("mlp_safety", C.c_float), ("sched", C.c_int32), ("sync_errors", C.c_int32),
-                ("d_features", C.c_void_p), ("debug_scale_mult", C.c_double),
+                ("debug_stall_it", C.c_int32), ("d_features", C.c_void_p), ("debug_scale_mult", C.c_double),
                 ("debug_poison_mol", C.c_int32), ("profile", C.c_int32),
                 ("ns_small_tile_mask", C.c_uint64), ("d_wcols", C.c_void_p),
                 ("inverse", C.c_int32), ("inv_max_iter", C.c_int32),

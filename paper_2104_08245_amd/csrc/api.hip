@@ -237,6 +237,7 @@ static LaunchArgs make_args(const nolsm_plan *pl, const BatchArgs &b) {
     na.sym = o.sym_sign ? 1 : 0;
     na.nt_out = 0;
     na.force_stall = o.debug_force_stall;
+    na.stall_it = o.debug_stall_it > 0 ? o.debug_stall_it : 2;
     InvArgs &ia = A.ia;
     ia.prec = o.prec;
     ia.max_iter = o.inv_max_iter;

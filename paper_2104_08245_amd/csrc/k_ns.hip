@@ -51,7 +51,7 @@ __device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const 
     // at one iteration, so that the restart path can be checked (every
     // workgroup of the submatrix takes the same decision from `it` alone;
     // restart_at may already hold it + 1 from the tile-0 workgroup)
-    const bool forced = na.force_stall >= 0 && M.J == na.force_stall && it == NOLSM_STALL_IT;
+    const bool forced = na.force_stall >= 0 && M.J == na.force_stall && it == na.stall_it;
     const bool diverge = forced || !isfinite(r) || (it >= 1 && r > 2.0 * rprev && r > 1.0);
     int act;
     bool noconv = false;
