@@ -503,7 +503,6 @@ extern "C" int nolsm_sign_batch(nolsm_plan *pl, const double *dK_val, const doub
             if (e != hipSuccess) return hip_fail(e, "graph instantiate");
             pl->graph_exec = ex;
             for (int i = 0; i < 6; ++i) pl->g_key[i] = key[i];
-            pl->g_mu = mu;
             pl->g_opts = *opts;
             pl->g_stream = stream;
         }

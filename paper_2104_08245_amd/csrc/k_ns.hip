@@ -85,11 +85,6 @@ __device__ int ns_decide(const NsArgs &na, const SubMeta &M, SubCtl *ctl, const 
     return act;
 }
 
-template <typename T> __device__ __forceinline__ T to_t(float x);
-template <> __device__ __forceinline__ double to_t<double>(float x) { return x; }
-template <> __device__ __forceinline__ float to_t<float>(float x) { return x; }
-template <typename T> __device__ __forceinline__ T to_t_d(double x) { return (T)x; }
-
 // X_{k+1} tile <- c_G A on [0,n)^2, identity on the padding (restart);
 // sym: from the upper triangle of A, so that the restart is exactly symmetric
 template <typename T, typename Cvt>
@@ -337,7 +332,12 @@ __device__ __forceinline__ void rest_of(SubCtl *ctl, int nt, int bstep, int it0,
     for (;;) {
         // one block of thread 0 a turn, with a barrier on either side of it:
         // no branch on the thread leads from the end of a turn to the next,
-        // so no wave goes round the loop without its first lane
+        // so no wave goes round the loop without its first lane. Keep it so.
+        // With a second block of thread 0 at the end of the turn (to count its
+        // tile), and no barrier between that and this one, the compiler joined
+        // the two: lanes 1 to 63 went on to the barriers of the next turn by
+        // themselves, and the kernel hung. It does not move a branch across a
+        // barrier.
         if (threadIdx.x == 0) {
             int k = __hip_atomic_fetch_add(&ctl->rest_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int half = k / ntile;

@@ -632,8 +632,8 @@ __global__ __launch_bounds__(256, 3) void k_chol_diag2(ChunkDev cd, char *ws, in
 // submatrices of about 612 rows, 28.8 for a slab of 2,048 (340 to 1,520 rows);
 // now 11.9 and 25.9.
 #define CHOL_PR 2
-template <typename T, int OCC>
-__global__ __launch_bounds__(256, OCC) void k_chol_panel2(ChunkDev cd, char *ws, int j, int ny) {
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_chol_panel2(ChunkDev cd, char *ws, int j, int ny) {
     typedef CholSlice<T> C;
     typedef typename C::vec vec;
     constexpr int BK = CHOL_BK, LD = C::LD, VE = C::VE, AL = C::AL, AR = C::AR, AP = C::AP, NX = CHOL_PR + 2;
@@ -1250,8 +1250,7 @@ __global__ __launch_bounds__(256, OCC) void k_subst_hl(ChunkDev cd, char *ws) {
 // submatrix and launch) every launch read the factor's lower triangle again
 // and few workgroups were in flight: 8.1 -> 7.1 ms for 4,096 submatrices of
 // about 612 rows, 21.7 -> 14.4 ms for a slab of 2,048 (340 to 1,520 rows).
-template <int OCC>
-__global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, int c) {
+__global__ __launch_bounds__(256, 2) void k_rsolve2_hl(ChunkDev cd, char *ws, int c) {
     const double mu = ((const WsHeader *)ws)->mu;
     __shared__ __attribute__((aligned(16))) HLTile sXa;   // operands of row i
     __shared__ __attribute__((aligned(16))) HLTile sXb;   // operands of row i + 1
@@ -1373,74 +1372,72 @@ __global__ __launch_bounds__(256, OCC) void k_rsolve2_hl(ChunkDev cd, char *ws, 
         }
     }
     if (j0 < P) {   // then row i + 1 is there too
-        {
-            constexpr int RC = 2;
-            const int nr = min(RC, P - j0);
-            AccT<float> a0[RC], a1[RC];
+        constexpr int RC = 2;
+        const int nr = min(RC, P - j0);
+        AccT<float> a0[RC], a1[RC];
 #pragma unroll
-            for (int r = 0; r < RC; ++r)
-                if (r < nr) {
-                    g2acc(a0[r], Xt(i, j0 + r), ldk);
-                    acc_mul(a0[r], sc);
-                    g2acc(a1[r], Xt(i + 1, j0 + r), ldk);
-                    acc_mul(a1[r], sc);
-                }
-            {
-                __syncthreads();
-                RegTile<float> pl;
-                g2r_tile(pl, Lt(j0, 0), ldl);
-                r2hl(sL, pl, 1.0f);
-                for (int k = 0; k < j0; ++k) {
-                    load_x(sXa, i, k);
-                    load_x(sXb, i + 1, k);
-                    __syncthreads();
-#pragma unroll
-                    for (int r = 0; r < RC; ++r) {
-                        if (r < nr) {
-                            const bool last_r = (r + 1 == nr);
-                            const int kn = last_r ? k + 1 : k, rn = last_r ? 0 : r + 1;
-                            const bool more = kn < j0;
-                            if (more) g2r_tile(pl, Lt(j0 + rn, kn), ldl);
-                            mma64_hl(a0[r], sXa, sL);
-                            mma64_hl(a1[r], sXb, sL);
-                            __syncthreads();
-                            if (more) r2hl(sL, pl, 1.0f);
-                            if (!last_r) __syncthreads();
-                        }
-                    }
-                }
-                __syncthreads();
+        for (int r = 0; r < RC; ++r)
+            if (r < nr) {
+                g2acc(a0[r], Xt(i, j0 + r), ldk);
+                acc_mul(a0[r], sc);
+                g2acc(a1[r], Xt(i + 1, j0 + r), ldk);
+                acc_mul(a1[r], sc);
             }
+        {
+            __syncthreads();
+            RegTile<float> pl;
+            g2r_tile(pl, Lt(j0, 0), ldl);
+            r2hl(sL, pl, 1.0f);
+            for (int k = 0; k < j0; ++k) {
+                load_x(sXa, i, k);
+                load_x(sXb, i + 1, k);
+                __syncthreads();
 #pragma unroll
-            for (int r = 0; r < RC; ++r) {
-                if (r < nr) {
-                    const int j = j0 + r;
-                    AccT<float> o0, o1;
-                    g2hl(sL, Dt(j), 64, 1.0f);
-                    acc2hl(sXa, a0[r], 1.0f);
-                    acc2hl(sXb, a1[r], 1.0f);
-                    __syncthreads();
-                    acc_zero(o0);
-                    acc_zero(o1);
-                    mma64_hl(o0, sXa, sL);
-                    mma64_hl(o1, sXb, sL);
-                    __syncthreads();
-                    acc2hl(sXa, o0, -1.0f);   // read by the next products only after emit's barriers
-                    emit(o0, i, j, frob0);
-                    acc2hl(sXb, o1, -1.0f);
-                    emit(o1, i + 1, j, frob1);
-#pragma unroll
-                    for (int r2 = r + 1; r2 < RC; ++r2) {
-                        if (r2 < nr) {
-                            g2hl(sL, Lt(j0 + r2, j), ldl, 1.0f);
-                            __syncthreads();
-                            mma64_hl(a0[r2], sXa, sL);
-                            mma64_hl(a1[r2], sXb, sL);
-                            __syncthreads();
-                        }
+                for (int r = 0; r < RC; ++r) {
+                    if (r < nr) {
+                        const bool last_r = (r + 1 == nr);
+                        const int kn = last_r ? k + 1 : k, rn = last_r ? 0 : r + 1;
+                        const bool more = kn < j0;
+                        if (more) g2r_tile(pl, Lt(j0 + rn, kn), ldl);
+                        mma64_hl(a0[r], sXa, sL);
+                        mma64_hl(a1[r], sXb, sL);
+                        __syncthreads();
+                        if (more) r2hl(sL, pl, 1.0f);
+                        if (!last_r) __syncthreads();
                     }
-                    __syncthreads();
                 }
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            if (r < nr) {
+                const int j = j0 + r;
+                AccT<float> o0, o1;
+                g2hl(sL, Dt(j), 64, 1.0f);
+                acc2hl(sXa, a0[r], 1.0f);
+                acc2hl(sXb, a1[r], 1.0f);
+                __syncthreads();
+                acc_zero(o0);
+                acc_zero(o1);
+                mma64_hl(o0, sXa, sL);
+                mma64_hl(o1, sXb, sL);
+                __syncthreads();
+                acc2hl(sXa, o0, -1.0f);   // read by the next products only after emit's barriers
+                emit(o0, i, j, frob0);
+                acc2hl(sXb, o1, -1.0f);
+                emit(o1, i + 1, j, frob1);
+#pragma unroll
+                for (int r2 = r + 1; r2 < RC; ++r2) {
+                    if (r2 < nr) {
+                        g2hl(sL, Lt(j0 + r2, j), ldl, 1.0f);
+                        __syncthreads();
+                        mma64_hl(a0[r2], sXa, sL);
+                        mma64_hl(a1[r2], sXb, sL);
+                        __syncthreads();
+                    }
+                }
+                __syncthreads();
             }
         }
     }
@@ -1716,7 +1713,7 @@ static hipError_t run_chol(const ChunkDev &cd, char *ws, hipStream_t st) {
         const int rows = pmax - 2 - j;
         if (rows <= 0) continue;
         const int ny = (rows + CHOL_PR - 1) / CHOL_PR;
-        hipLaunchKernelGGL((k_chol_panel2<T, 2>), parts_grid(cd.nsub, ny), dim3(256), 0, st, cd, ws, j, ny);
+        hipLaunchKernelGGL(k_chol_panel2<T>, parts_grid(cd.nsub, ny), dim3(256), 0, st, cd, ws, j, ny);
         LAUNCH_CHECK();
     }
     return hipSuccess;
@@ -1741,7 +1738,7 @@ hipError_t launch_subst_sym(const ChunkDev &cd, char *ws, bool fp32, bool split1
     const int pmax = cd.max_np / 64;
     if (hl) {
         for (int c = 1; c <= (pmax + 1) / 2; ++c) {
-            hipLaunchKernelGGL(k_rsolve2_hl<2>, parts_grid(cd.nsub, c), dim3(256), 0, st, cd, ws, c);
+            hipLaunchKernelGGL(k_rsolve2_hl, parts_grid(cd.nsub, c), dim3(256), 0, st, cd, ws, c);
             LAUNCH_CHECK();
         }
         return hipSuccess;

@@ -56,7 +56,6 @@ struct nolsm_plan {
     // graph cache
     void *graph_exec = nullptr;
     const void *g_key[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    double g_mu = 0.0;
     nolsm_solve_opts g_opts;
     void *g_stream = nullptr;
     // pipeline schedule: the library's second stream and its order events
